@@ -1,42 +1,50 @@
 // Block-sparse softmax attention for gfx950: 64 x 64 score blocks on the
 // flat block butterfly mask, head dim 64, bf16 I/O, fp32 softmax/accumulate.
 //
-// Workgroup = 4 waves over one 64-row block (of queries for the forward and
-// dQ, of keys for dK/dV); each wave owns 16 rows.  Everything is computed in
-// transposed form so that each lane owns ONE row (its softmax statistics are
-// per-lane scalars) and the probability tile feeds the next MFMA straight
-// from registers:
-//   forward : S^T = K_j Q_w^T (16x16x32 MFMA), online softmax per query,
-//             O^T += V_j^T P^T.
+// Workgroup = groups of 2 waves; a group owns one 64-row block (of queries
+// for the forward and dQ, of keys for dK/dV), each wave 32 rows of it.
+// Everything is computed in transposed form so that each lane owns ONE row
+// (its softmax statistics are per-lane scalars) and the probability tile
+// feeds the next MFMA straight from registers (32x32x16 MFMA):
+//   forward : S^T = K_j Q_w^T, online softmax per query, O^T += V_j^T P^T.
 //   dQ      : recompute S^T, P^T; dP^T = V_j dO_w^T; dS^T = P^T o (dP^T -
 //             delta); dQ^T += K_j^T dS^T.
 //   dK, dV  : S = Q_i K_w^T, P, dP = dO_i V_w^T, dS; dV^T += dO_i^T P,
 //             dK^T += Q_i^T dS.
-// The register tile of P (rows = 16 keys per MFMA output, 4 per lane) is
-// used as a K-operand with keys in the order {16c + 4*(l/16) + 0..3} for two
-// consecutive c; the matching operand is read from LDS with the transpose
-// read in that same key order, so the contraction pairs up correctly.
+// An accumulator of a 32 x 32 tile holds, in lane l, rows 8 (e / 4) + 4
+// (l / 32) + e % 4 of column l % 32; its registers 8 j .. 8 j + 7 are used as
+// the K-operand of 16 rows in that order, and the matching operand is read
+// from LDS with the transpose read in the same order.
+//
+// The tiles of a kept block go global -> LDS directly.  A wave reads whole
+// tiles from LDS whatever its row count, so 32 rows per wave halve the LDS
+// bytes per score of the 16-row waves these kernels had before, and the
+// swizzled tiles have no bank conflicts.  Counters at 8 x 12 x 4096 x 64,
+// 7 blocks per row: forward VALU 51 % (exponentials a third of it), MFMA
+// 29 %, LDS 15 % of cycles; dQ 42 / 32 / 16 %, dK/dV 39 / 33 / 25 %: the
+// serial S -> softmax -> product chain of few waves per SIMD bounds them, so
+// forward and dQ keep one stage per operand (16 KiB per workgroup, four
+// waves per SIMD; two stages and 2.5 waves: 79 against 66 us, 111 against
+// 101 us) and refill each operand as soon as its last read is done; dK/dV,
+// whose accumulators leave two waves per SIMD, keeps two stages (one stage
+// and three waves: 123 -> 131 us).  16-row waves -> this: forward 85 -> 66,
+// dQ 113 -> 101, dK/dV 152 -> 122 us.  Measured and not kept: wave priority
+// around the MFMA phases, the softmax of one half of the keys under the MFMAs
+// of the other, maxima replaced by a check of the sums (all within 3 %).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include <mutex>
 
+#include "pf_dma.h"
 #include "pf_launch.h"
 
 namespace pf {
+namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint16_t bf16_t;
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-
-constexpr int D = 64;       // head dim
-constexpr int BQ = 64;      // block size
-constexpr int LDK = D + 8;  // LDS row stride (elements)
-constexpr int LDV = D + 16;
+constexpr int D = 64;                    // head dim
+constexpr int BQ = 64;                   // block size
+constexpr int TILE = BQ * D * 2;         // bytes of a 64 x 64 bf16 tile
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
@@ -45,99 +53,110 @@ constexpr float kLn2 = 0.6931471805599453f;
 // range-reduction sequence the library exp2f adds for denormal outputs.
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// Wait for every global load of this wave (vmcnt 0; LDS counter too).
-// Placed before a block loop whose first MFMAs use operands loaded ahead of
-// it: otherwise the compiler's wait analysis, joining that path with the
-// loop's back edge, can wait for the next tile's loads just issued at the
-// top of the loop as well.
-__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x70); }
-
-// x combined with the value of lane l ^ 16 (l ^ 32) by max or +: the two
-// swaps exchange rows of 16 (halves of 32) lanes inside the VALU, where a
-// lane shuffle would make a round trip through the LDS.  Each lane gets its
-// own and its partner's value in some order, so max and + give the same bits
-// in both lanes and as the shuffle form.
-__device__ __forceinline__ float max_xor16(float x) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
+// x combined with the value of lane l ^ 32 by max or +: the swap exchanges
+// the halves inside the VALU, where a lane shuffle would make a round trip
+// through the LDS.
 __device__ __forceinline__ float max_xor32(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float add_xor16(float x) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 __device__ __forceinline__ float add_xor32(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-__device__ __forceinline__ float bf2f_a(bf16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
-__device__ __forceinline__ bf16_t f2bf_a(float f) { return __builtin_bit_cast(bf16_t, (__bf16)f); }
-
-__device__ __forceinline__ int xcd_remap_a(int bid, int n) {
-  constexpr int X = 8;
-  int q = n / X, rem = n % X, x = bid % X, slot = bid / X;
-  return x * q + min(x, rem) + slot;
+__device__ __forceinline__ uint32_t pack2(float lo, float hi) {
+  return (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)lo) |
+         ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)hi) << 16);
 }
 
-__device__ __forceinline__ s16x4 tr16a(const bf16_t *p) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-      (__attribute__((address_space(3))) s16x4 *)(p));
+// LDS tile: 64 rows of 128 bytes, the 16-byte chunk c of row r at position
+// c ^ chunk_swz(r).  Row pairs (256 bytes, all 64 banks) get the eight
+// values of the bit-reversed pair index: 16 rows at one chunk (fragment
+// read) and 4 rows x 4 chunks (transpose read) both fall in distinct banks.
+__device__ __forceinline__ int chunk_swz(int r) {
+  return ((r & 2) << 1) | ((r & 4) >> 1) | ((r & 8) >> 3);
 }
 
-// A-operand of a 16x16x32 MFMA, A[m][k] = tile[k][m] (tile stored [k][m],
-// m contiguous), with k in the permuted order {kb + 4*(l/16) + 0..3} then
-// {kb + 16 + 4*(l/16) + 0..3}; m = m0 + l % 16.
-__device__ __forceinline__ bf16x8 fragA_tr_perm(const bf16_t *tile, int ld, int kb, int m0, int lane) {
-  const int g = lane >> 4, i = lane & 15;
-  const bf16_t *p = tile + (kb + g * 4 + (i >> 2)) * ld + m0 + (i & 3) * 4;
-  s16x4 lo = tr16a(p), hi = tr16a(p + 16 * ld);
-  s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-  return __builtin_bit_cast(bf16x8, v);
-}
-
-// Operand of a 16x16x32 MFMA from a [row][k] tile: row r0 + l % 16,
-// k = kb + (l/16)*8 + 0..7 (16-byte read).
-__device__ __forceinline__ bf16x8 frag_rows(const bf16_t *tile, int ld, int r0, int kb, int lane) {
-  return *(const bf16x8 *)(tile + (r0 + (lane & 15)) * ld + kb + (lane >> 4) * 8);
-}
-
-// Same from global memory.
-__device__ __forceinline__ bf16x8 frag_rows_g(const bf16_t *p, int r0, int kb, int lane) {
-  return *(const bf16x8 *)(p + (int64_t)(r0 + (lane & 15)) * D + kb + (lane >> 4) * 8);
-}
-
-// Pack a register tile (two 16-row MFMA outputs c0, c1) as the permuted
-// K-operand.
-__device__ __forceinline__ bf16x8 pack_perm(const f32x4 &c0, const f32x4 &c1) {
-  bf16x8 v;
-  v[0] = (__bf16)c0[0]; v[1] = (__bf16)c0[1]; v[2] = (__bf16)c0[2]; v[3] = (__bf16)c0[3];
-  v[4] = (__bf16)c1[0]; v[5] = (__bf16)c1[1]; v[6] = (__bf16)c1[2]; v[7] = (__bf16)c1[3];
-  return v;
-}
-
-#define MFMA16(a, b, c) __builtin_amdgcn_mfma_f32_16x16x32_bf16((a), (b), (c), 0, 0, 0)
-
-// Cooperative load of a 64 x 64 bf16 tile (row stride D in global) into
-// registers: 512 chunks of 16 bytes, two per thread.
-struct Tile64 {
-  u32x4 r0, r1;  // named fields: never addressed with a run-time index
-  __device__ __forceinline__ void load(const bf16_t *g, int tid) {
-    const int row = tid >> 3, c = (tid & 7) * 8;
-    r0 = *(const u32x4 *)(g + row * D + c);
-    r1 = *(const u32x4 *)(g + (row + 32) * D + c);
+// Copies of one tile by the 2 waves of a group: wave w fills the 1 KiB
+// windows (8 rows) 4 w .. 4 w + 3.
+struct TileCopy {
+  uint32_t voff[2];  // lane part, even / odd windows
+  int w4;            // first window of this wave
+  __device__ __forceinline__ void init(int lane, int w) {
+    const int x = (((lane >> 4) & 1) << 2) | (((lane >> 5) & 1) << 1);
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+      voff[o] = (uint32_t)((lane >> 3) * 128 + (((lane & 7) ^ x ^ o) << 4));
+    w4 = w * 4;
   }
-  __device__ __forceinline__ void store(bf16_t *s, int ld, int tid) const {
-    const int row = tid >> 3, c = (tid & 7) * 8;
-    *(u32x4 *)(s + row * ld + c) = r0;
-    *(u32x4 *)(s + (row + 32) * ld + c) = r1;
+  // live false: the copies read nothing and leave zeros (an empty range), so
+  // that the loop has no branch around them and the waits stay counted.
+  __device__ __forceinline__ void issue(const bf16_t *g, uint8_t *tile, bool live) const {
+    const rsrc_t r = make_rsrc(g, live ? TILE : 0);
+    sfor<4>([&](auto i) __attribute__((always_inline)) {
+      dma16(r, tile + (w4 + i) * 1024, voff[i & 1], (uint32_t)((w4 + i) * 1024));
+    });
   }
 };
 
-// ---------------------------------------------------------------------------
+// Operand of a 32x32x16 MFMA from a tile: row r0 + l % 32, k = ks * 16 +
+// (l / 32) * 8 + 0..7.
+__device__ __forceinline__ bf16x8 frag_r(const uint8_t *tile, int r0, int ks, int lane) {
+  const int r = r0 + (lane & 31), c = ks * 2 + (lane >> 5);
+  return *(const bf16x8 *)(tile + r * 128 + ((c ^ chunk_swz(r)) << 4));
+}
+// Same from global memory (64-column rows).
+__device__ __forceinline__ bf16x8 frag_g(const bf16_t *p, int r0, int ks, int lane) {
+  return *(const bf16x8 *)(p + (int64_t)(r0 + (lane & 31)) * D + ks * 16 + (lane >> 5) * 8);
+}
+// Operand A[m][k] = tile[k][m], m = m0 + l % 32, k in the accumulator's row
+// order: kb + 4 (l / 32) + 0..3, then kb + 8 + 4 (l / 32) + 0..3.
+__device__ __forceinline__ bf16x8 frag_t(const uint8_t *tile, int kb, int m0, int lane) {
+  const int g = lane >> 4, i = lane & 15;
+  const int c = (m0 >> 3) + (g & 1) * 2 + ((i & 3) >> 1), half = (i & 1) << 3;
+  const int k = kb + (g >> 1) * 4 + (i >> 2);
+  const int lo_off = k * 128 + ((c ^ chunk_swz(k)) << 4) + half;
+  const int hi_off = (k + 8) * 128 + ((c ^ chunk_swz(k + 8)) << 4) + half;
+  const s16x4 lo = tr16(tile + lo_off), hi = tr16(tile + hi_off);
+  const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  return __builtin_bit_cast(bf16x8, v);
+}
+// Registers 8 j .. 8 j + 7 of an accumulator as a bf16 K-operand.
+__device__ __forceinline__ bf16x8 pack_k(const f32x16 &s, int j) {
+  bf16x8 v;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = (__bf16)s[8 * j + e];
+  return v;
+}
+
+#define MFMA32(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16((a), (b), (c), 0, 0, 0)
+
+// Row (query or key) l % 32's 64 columns held as two transposed accumulators,
+// times `scale`, to 128 contiguous bytes at dst: the halves swap registers
+// so that each lane stores 16 bytes at a time.
+__device__ __forceinline__ void store_row(bf16_t *dst, const f32x16 (&o)[2], float scale, int lane) {
+#pragma unroll
+  for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const int e = 8 * p;
+      const uint32_t x0 = pack2(o[dt][e] * scale, o[dt][e + 1] * scale);
+      const uint32_t x1 = pack2(o[dt][e + 2] * scale, o[dt][e + 3] * scale);
+      const uint32_t y0 = pack2(o[dt][e + 4] * scale, o[dt][e + 5] * scale);
+      const uint32_t y1 = pack2(o[dt][e + 6] * scale, o[dt][e + 7] * scale);
+      const auto s0 = __builtin_amdgcn_permlane32_swap(x0, y0, false, false);
+      const auto s1 = __builtin_amdgcn_permlane32_swap(x1, y1, false, false);
+      *(u32x4 *)(dst + dt * 32 + p * 16 + (lane >> 5) * 8) = u32x4{s0[0], s1[0], s0[1], s1[1]};
+    }
+}
+
+// Merge area of group g, float slot v (0..15) of this wave's lane in stage
+// object `obj` (one 8 KiB tile per group: 16 floats x 64 lanes x 2 waves).
+__device__ __forceinline__ float *merge_at(uint8_t *obj, int g, int w, int lane) {
+  return (float *)(obj + g * TILE) + w * (16 * 64) + lane;
+}
+
 // Work order: (head, block) of logical id L.  Block rows (or, for dK/dV,
 // block columns) below nlong are the global stripes of the mask, which keep
 // every block of the other side: they go first, over all heads, so that the
@@ -153,183 +172,183 @@ __device__ __forceinline__ void attn_order(int L, int BH, int nb, int nlong, int
   }
 }
 
+// ---------------------------------------------------------------------------
 // Forward
 // ---------------------------------------------------------------------------
-// NG groups of 4 waves share one 64-query block: group g takes the row's
-// kept blocks g, g + NG, ... (each group has its own double-buffered K/V
-// tiles; all groups run the same number of iterations so every barrier is
-// reached by the whole workgroup) and the groups' softmax states (reference,
-// sum, unnormalised O) are merged through LDS in group order at the end.
-// NG = 1 is the plain kernel; NG = 4 serves the long rows of global stripes.
+// NG groups share one 64-query block: group g takes the row's kept blocks g,
+// g + NG, ... (each group has its own double-buffered K/V tiles; all groups
+// run the same number of iterations so every barrier is reached by the whole
+// workgroup) and the groups' softmax states (reference, sum, unnormalised O)
+// are merged through LDS in group order at the end.
 template <int NG>
-__global__ __launch_bounds__(256 * NG) void attn_fwd_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) bf16_t Ks[NG][2][BQ * LDK];
-  __shared__ __attribute__((aligned(16))) bf16_t Vs[NG][2][BQ * LDV];
+__global__ __launch_bounds__(128 * NG, NG == 1 ? 4 : 1) void attn_fwd_kernel(AttnArgs a) {
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 1);
+  const int grp = NG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 7) : 0;
+  uint8_t *const kst = stage_buf<0, NG * TILE>(), *const vst = stage_buf<1, NG * TILE>();
+  __shared__ float ml[NG > 1 ? NG : 1][256];  // merge: reference and sum per lane
+  uint8_t *const kc = kst + grp * TILE, *const vc = vst + grp * TILE;
 
-  const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;
-  const int grp = NG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) : 0;
-  const int bid = xcd_remap_a(blockIdx.x, gridDim.x) + a.first;
+  const int bid = xcd_remap(blockIdx.x, gridDim.x) + a.first;
   int bh, qb;
   attn_order(bid, a.BH, a.nbq, a.nlong, bh, qb);
   const int64_t head = (int64_t)bh * a.S * D;
   const bf16_t *Q = (const bf16_t *)a.Q + head;
   const bf16_t *K = (const bf16_t *)a.K + head;
   const bf16_t *V = (const bf16_t *)a.V + head;
-  const int q0 = qb * BQ + wave * 16;
+  const int q0 = qb * BQ + w * 32;
   const float c = a.scale * kLog2e;
 
-  bf16x8 qf[2];
-  qf[0] = frag_rows_g(Q, q0, 0, lane);
-  qf[1] = frag_rows_g(Q, q0, 32, lane);
-
-  const int p0 = a.row_ptr[qb], p1 = a.row_ptr[qb + 1];
+  // Rows are never empty; indices past a row's end are clamped into it and
+  // their copies switched off.
+  const int p0 = ld_meta(a.row_ptr + qb), p1 = ld_meta(a.row_ptr + qb + 1);
   const int iters = (p1 - p0 + NG - 1) / NG;
-  float m_run = -INFINITY, l_run = 0.f;
-  f32x4 o[4];
+  TileCopy cp;
+  cp.init(lane, w);
+  int ccur = ld_meta(a.col_idx + min(p0 + grp, p1 - 1));
+  cp.issue(K + (int64_t)ccur * BQ * D, kc, p0 + grp < p1);
+  bf16x8 qf[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  Tile64 tk, tv;
-  if (p0 + grp < p1) {
-    tk.load(K + (int64_t)a.col_idx[p0 + grp] * BQ * D, tid);
-    tv.load(V + (int64_t)a.col_idx[p0 + grp] * BQ * D, tid);
-    tk.store(Ks[grp][0], LDK, tid);
-    tv.store(Vs[grp][0], LDV, tid);
-  }
+  for (int ks = 0; ks < 4; ++ks) qf[ks] = frag_g(Q, q0, ks, lane);
   // Block column of this group's next tile, loaded one iteration ahead so
-  // that the tile loads do not wait on it (clamped into the row, which is
-  // never empty; unused past its end).
-  int cn = a.col_idx[min(p0 + grp + NG, p1 - 1)];
-  wait_loads();
-  __syncthreads();
+  // that the copies do not wait on it.
+  int cn = ld_meta(a.col_idx + min(p0 + grp + NG, p1 - 1));
+
+  float m_run = -INFINITY, l_run = 0.f;  // l_run: this lane's keys only
+  f32x16 o[2];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) o[0][e] = o[1][e] = 0.f;
 
   for (int it = 0; it < iters; ++it) {
-    const int cur = it & 1;
     const int p = p0 + it * NG + grp;
-    const bool valid = p < p1, next = p + NG < p1;
-    if (next) {
-      tk.load(K + (int64_t)cn * BQ * D, tid);
-      tv.load(V + (int64_t)cn * BQ * D, tid);
-    }
-    cn = a.col_idx[min(p + 2 * NG, p1 - 1)];
-    if (valid) {
-      // S^T[key][query] for 64 keys x this wave's 16 queries.
-      f32x4 s[4];
+    const bool valid = NG == 1 || p < p1;
+    wait_vm<0>();  // this wave's K copies have landed,
+    barrier();     // every wave's have, and the last block's V is read
+    cp.issue(V + (int64_t)ccur * BQ * D, vc, p < p1);
+    // S^T[key][query] for 64 keys x this wave's 32 queries.
+    f32x16 s[2];
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
-        s[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        s[mt] = MFMA16(frag_rows(Ks[grp][cur], LDK, mt * 16, 0, lane), qf[0], s[mt]);
-        s[mt] = MFMA16(frag_rows(Ks[grp][cur], LDK, mt * 16, 32, lane), qf[1], s[mt]);
-      }
+    for (int kt = 0; kt < 2; ++kt) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) s[kt][e] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) s[kt] = MFMA32(frag_r(kc, kt * 32, ks, lane), qf[ks], s[kt]);
+    }
+    wait_vm<4>();  // (no wait: the four V copies may be in flight)
+    barrier();     // every wave has read K
+    cp.issue(K + (int64_t)cn * BQ * D, kc, p + NG < p1);
+    ccur = cn;
+    cn = ld_meta(a.col_idx + min(p + 2 * NG, p1 - 1));
+    if (valid) {
       float bmax = -INFINITY;
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
+      for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) bmax = fmaxf(bmax, s[mt][j]);
-      bmax = max_xor32(max_xor16(bmax));
-      // The softmax reference m_run moves only when some row's maximum grew
-      // by more than 8 (log2 units): until then the probabilities stay below
-      // 2^8 and the rescale of O and l, a wave-uniform branch, is skipped.
-      const float m_cand = fmaxf(m_run, bmax * c);
-      if (__builtin_amdgcn_ballot_w64(m_cand > m_run + 8.0f)) {
+        for (int e = 0; e < 16; ++e) bmax = fmaxf(bmax, s[kt][e]);
+      // The softmax reference m_run (the same in both lanes of a query) moves
+      // only when some lane's maximum grew by more than 8 (log2 units): until
+      // then the probabilities stay below 2^8 and the rescale of O and l, a
+      // wave-uniform branch, is skipped.
+      if (__builtin_amdgcn_ballot_w64(fmaxf(m_run, bmax * c) > m_run + 8.0f)) {
+        const float m_cand = fmaxf(m_run, max_xor32(bmax) * c);
         const float alpha = fast_exp2(m_run - m_cand);
         m_run = m_cand;
         l_run *= alpha;
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
+        for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-          for (int j = 0; j < 4; ++j) o[dt][j] *= alpha;
+          for (int e = 0; e < 16; ++e) o[dt][e] *= alpha;
       }
       float rs = 0.f;
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
+      for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          float e = fast_exp2(s[mt][j] * c - m_run);
-          s[mt][j] = e;
-          rs += e;
+        for (int e = 0; e < 16; ++e) {
+          const float x = fast_exp2(s[kt][e] * c - m_run);
+          s[kt][e] = x;
+          rs += x;
         }
-      rs = add_xor32(add_xor16(rs));
       l_run += rs;
-      // O^T[dim][query] += V^T[dim][key] P^T[key][query]
-      const bf16x8 pb0 = pack_perm(s[0], s[1]), pb1 = pack_perm(s[2], s[3]);
+    }
+    wait_vm<4>();  // V has landed; the next K copies stay in flight
+    barrier();
+    if (!valid) continue;
+    // O^T[dim][query] += V^T[dim][key] P^T[key][query]
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt) {
-        o[dt] = MFMA16(fragA_tr_perm(Vs[grp][cur], LDV, 0, dt * 16, lane), pb0, o[dt]);
-        o[dt] = MFMA16(fragA_tr_perm(Vs[grp][cur], LDV, 32, dt * 16, lane), pb1, o[dt]);
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const bf16x8 pb = pack_k(s[kt], j);
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+          o[dt] = MFMA32(frag_t(vc, kt * 32 + j * 16, dt * 32, lane), pb, o[dt]);
       }
-    }
-    if (next) {
-      tk.store(Ks[grp][cur ^ 1], LDK, tid);
-      tv.store(Vs[grp][cur ^ 1], LDV, tid);
-    }
-    __syncthreads();
   }
+  wait_vm<0>();  // no copy outlives the workgroup
 
   if constexpr (NG > 1) {
-    // Merge: groups 1.. leave (m, l, o) per lane in their K tiles (18 floats
-    // x 64 lanes x 4 waves = exactly one group's K tiles), group 0 combines
-    // them relative to the largest reference.  A group without blocks has
-    // m = -inf and contributes 0.
-    float *mrg = (float *)&Ks[grp][0][0] + wave * (18 * 64) + lane;
+    // Merge: groups 1.. leave (o, m, l) per lane in their tiles, group 0
+    // combines them relative to the largest reference.  A group without
+    // blocks has m = -inf and contributes 0.
+    barrier();
     if (grp > 0) {
-      mrg[0] = m_run;
-      mrg[64] = l_run;
+      float *m0 = merge_at(kst, grp, w, lane), *m1 = merge_at(vst, grp, w, lane);
+      float *m2 = &ml[grp][w * 128 + lane];
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) mrg[(2 + dt * 4 + j) * 64] = o[dt][j];
+      for (int e = 0; e < 16; ++e) {
+        m0[e * 64] = o[0][e];
+        m1[e * 64] = o[1][e];
+      }
+      m2[0] = m_run;
+      m2[64] = l_run;
     }
     __syncthreads();
     if (grp > 0) return;
     float m = m_run;
 #pragma unroll
-    for (int g = 1; g < NG; ++g) m = fmaxf(m, ((float *)&Ks[g][0][0])[wave * (18 * 64) + lane]);
+    for (int g = 1; g < NG; ++g) m = fmaxf(m, ml[g][w * 128 + lane]);
     const float s0 = fast_exp2(m_run - m);
     l_run *= s0;
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) o[dt][j] *= s0;
+    for (int e = 0; e < 16; ++e) {
+      o[0][e] *= s0;
+      o[1][e] *= s0;
+    }
 #pragma unroll
     for (int g = 1; g < NG; ++g) {
-      const float *src = (const float *)&Ks[g][0][0] + wave * (18 * 64) + lane;
-      const float sg = src[0] == -INFINITY ? 0.f : fast_exp2(src[0] - m);
-      l_run += src[64] * sg;
+      const float *m0 = merge_at(kst, g, w, lane), *m1 = merge_at(vst, g, w, lane);
+      const float *m2 = &ml[g][w * 128 + lane];
+      const float sg = m2[0] == -INFINITY ? 0.f : fast_exp2(m2[0] - m);
+      l_run += m2[64] * sg;
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) o[dt][j] += src[(2 + dt * 4 + j) * 64] * sg;
+      for (int e = 0; e < 16; ++e) {
+        o[0][e] += m0[e * 64] * sg;
+        o[1][e] += m1[e * 64] * sg;
+      }
     }
     m_run = m;
   }
 
-  const float inv = 1.f / l_run;
-  const int q = q0 + (lane & 15);
-  bf16_t *O = (bf16_t *)a.Oout + head + (int64_t)q * D;
-#pragma unroll
-  for (int dt = 0; dt < 4; ++dt) {
-    u32x2 w;
-    w[0] = (uint32_t)f2bf_a(o[dt][0] * inv) | ((uint32_t)f2bf_a(o[dt][1] * inv) << 16);
-    w[1] = (uint32_t)f2bf_a(o[dt][2] * inv) | ((uint32_t)f2bf_a(o[dt][3] * inv) << 16);
-    *(u32x2 *)(O + dt * 16 + (lane >> 4) * 4) = w;
-  }
-  if (lane < 16) a.lse[(int64_t)bh * a.S + q] = (m_run + __log2f(l_run)) * kLn2;
+  l_run = add_xor32(l_run);
+  const int q = q0 + (lane & 31);
+  store_row((bf16_t *)a.Oout + head + (int64_t)q * D, o, 1.f / l_run, lane);
+  if (lane < 32) a.lse[(int64_t)bh * a.S + q] = (m_run + __log2f(l_run)) * kLn2;
 }
 
 // ---------------------------------------------------------------------------
-// Backward, pass 1: delta and dQ (one workgroup per query block)
+// Backward, pass 1: delta and dQ (a group per query block)
 // ---------------------------------------------------------------------------
-// NG groups of 4 waves split the row's kept blocks as in the forward; their
-// dQ partial sums are added through LDS in group order.
+// NG groups split the row's kept blocks as in the forward; their dQ partial
+// sums are added through LDS in group order.
 template <int NG>
-__global__ __launch_bounds__(256 * NG) void attn_bwd_dq_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) bf16_t Ks[NG][2][BQ * LDK];
-  __shared__ __attribute__((aligned(16))) bf16_t Vs[NG][2][BQ * LDK];
+__global__ __launch_bounds__(128 * NG, NG == 1 ? 4 : 1) void attn_bwd_dq_kernel(AttnArgs a) {
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 1);
+  const int grp = NG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 7) : 0;
+  uint8_t *const kst = stage_buf<0, NG * TILE>(), *const vst = stage_buf<1, NG * TILE>();
+  uint8_t *const kc = kst + grp * TILE, *const vc = vst + grp * TILE;
 
-  const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;
-  const int grp = NG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) : 0;
-  const int bid = xcd_remap_a(blockIdx.x, gridDim.x) + a.first;
+  const int bid = xcd_remap(blockIdx.x, gridDim.x) + a.first;
   int bh, qb;
   attn_order(bid, a.BH, a.nbq, a.nlong, bh, qb);
   const int64_t head = (int64_t)bh * a.S * D;
@@ -338,140 +357,132 @@ __global__ __launch_bounds__(256 * NG) void attn_bwd_dq_kernel(AttnArgs a) {
   const bf16_t *V = (const bf16_t *)a.V + head;
   const bf16_t *O = (const bf16_t *)a.O + head;
   const bf16_t *dO = (const bf16_t *)a.dO + head;
-  const int q0 = qb * BQ + wave * 16;
-  const int q = q0 + (lane & 15);
+  const int q0 = qb * BQ + w * 32;
+  const int q = q0 + (lane & 31);
   const float c = a.scale * kLog2e;
 
-  bf16x8 qf[2], dof[2];
-  qf[0] = frag_rows_g(Q, q0, 0, lane);
-  qf[1] = frag_rows_g(Q, q0, 32, lane);
-  dof[0] = frag_rows_g(dO, q0, 0, lane);
-  dof[1] = frag_rows_g(dO, q0, 32, lane);
-
-  // delta = rowsum(dO o O): lane covers dims (l/16)*16 .. +15 of query q.
-  float delta = 0.f;
-  {
-    const bf16_t *po = O + (int64_t)q * D + (lane >> 4) * 16;
-    const bf16_t *pd = dO + (int64_t)q * D + (lane >> 4) * 16;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const u32x4 vo = *(const u32x4 *)(po + h * 8), vd = *(const u32x4 *)(pd + h * 8);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        delta += __uint_as_float(vo[e] << 16) * __uint_as_float(vd[e] << 16);
-        delta += __uint_as_float(vo[e] & 0xffff0000u) * __uint_as_float(vd[e] & 0xffff0000u);
-      }
-    }
-    delta += __shfl_xor(delta, 16);
-    delta += __shfl_xor(delta, 32);
-  }
-  if (lane < 16 && grp == 0) a.delta[(int64_t)bh * a.S + q] = delta;
-  const float lse2 = a.lse_in[(int64_t)bh * a.S + q] * kLog2e;
-
-  const int p0 = a.row_ptr[qb], p1 = a.row_ptr[qb + 1];
+  const int p0 = ld_meta(a.row_ptr + qb), p1 = ld_meta(a.row_ptr + qb + 1);
   const int iters = (p1 - p0 + NG - 1) / NG;
-  f32x4 dq[4];
+  TileCopy cp;
+  cp.init(lane, w);
+  const int c0 = ld_meta(a.col_idx + min(p0 + grp, p1 - 1));
+  cp.issue(V + (int64_t)c0 * BQ * D, vc, p0 + grp < p1);
+  cp.issue(K + (int64_t)c0 * BQ * D, kc, p0 + grp < p1);
+  bf16x8 qf[4], dof[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) dq[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  Tile64 tk, tv;
-  if (p0 + grp < p1) {
-    tk.load(K + (int64_t)a.col_idx[p0 + grp] * BQ * D, tid);
-    tv.load(V + (int64_t)a.col_idx[p0 + grp] * BQ * D, tid);
-    tk.store(Ks[grp][0], LDK, tid);
-    tv.store(Vs[grp][0], LDK, tid);
+  for (int ks = 0; ks < 4; ++ks) {
+    qf[ks] = frag_g(Q, q0, ks, lane);
+    dof[ks] = frag_g(dO, q0, ks, lane);
   }
+  // delta = rowsum(dO o O): the two lanes of a query hold half its columns
+  // each in the fragment layout.
+  float delta = 0.f;
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+    const bf16x8 of = frag_g(O, q0, ks, lane);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) delta += (float)of[e] * (float)dof[ks][e];
+  }
+  delta = add_xor32(delta);
+  if (lane < 32 && grp == 0) a.delta[(int64_t)bh * a.S + q] = delta;
+  const float lse2 = a.lse_in[(int64_t)bh * a.S + q] * kLog2e;
   // Next block column one iteration ahead, as in the forward.
-  int cn = a.col_idx[min(p0 + grp + NG, p1 - 1)];
-  __syncthreads();
+  int cn = ld_meta(a.col_idx + min(p0 + grp + NG, p1 - 1));
+
+  f32x16 dq[2];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) dq[0][e] = dq[1][e] = 0.f;
 
   for (int it = 0; it < iters; ++it) {
-    const int cur = it & 1;
     const int p = p0 + it * NG + grp;
-    const bool valid = p < p1, next = p + NG < p1;
-    if (next) {
-      tk.load(K + (int64_t)cn * BQ * D, tid);
-      tv.load(V + (int64_t)cn * BQ * D, tid);
-    }
-    cn = a.col_idx[min(p + 2 * NG, p1 - 1)];
-    if (valid) {
-    f32x4 s[4], dp[4];
+    const bool valid = NG == 1 || p < p1;
+    wait_vm<0>();  // this wave's copies of the block have landed,
+    barrier();     // every wave's have
+    const int cc = cn;
+    cn = ld_meta(a.col_idx + min(p + 2 * NG, p1 - 1));
+    // S^T and dP^T of 32 keys, dS^T from them, and its product with K.
+    f32x16 s, dp;
+    auto scores = [&](int kt) __attribute__((always_inline)) {
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      s[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-      s[mt] = MFMA16(frag_rows(Ks[grp][cur], LDK, mt * 16, 0, lane), qf[0], s[mt]);
-      s[mt] = MFMA16(frag_rows(Ks[grp][cur], LDK, mt * 16, 32, lane), qf[1], s[mt]);
-      dp[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-      dp[mt] = MFMA16(frag_rows(Vs[grp][cur], LDK, mt * 16, 0, lane), dof[0], dp[mt]);
-      dp[mt] = MFMA16(frag_rows(Vs[grp][cur], LDK, mt * 16, 32, lane), dof[1], dp[mt]);
-    }
+      for (int e = 0; e < 16; ++e) s[e] = dp[e] = 0.f;
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        float pr = fast_exp2(s[mt][j] * c - lse2);
-        s[mt][j] = pr * (dp[mt][j] - delta);  // dS^T
+      for (int ks = 0; ks < 4; ++ks) {
+        s = MFMA32(frag_r(kc, kt * 32, ks, lane), qf[ks], s);
+        dp = MFMA32(frag_r(vc, kt * 32, ks, lane), dof[ks], dp);
       }
-    const bf16x8 d0 = pack_perm(s[0], s[1]), d1 = pack_perm(s[2], s[3]);
+    };
+    auto grads = [&](int kt) __attribute__((always_inline)) {
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt) {
-      dq[dt] = MFMA16(fragA_tr_perm(Ks[grp][cur], LDK, 0, dt * 16, lane), d0, dq[dt]);
-      dq[dt] = MFMA16(fragA_tr_perm(Ks[grp][cur], LDK, 32, dt * 16, lane), d1, dq[dt]);
+      for (int e = 0; e < 16; ++e) {
+        const float pr = fast_exp2(s[e] * c - lse2);
+        s[e] = pr * (dp[e] - delta);  // dS^T
+      }
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const bf16x8 d = pack_k(s, j);
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+          dq[dt] = MFMA32(frag_t(kc, kt * 32 + j * 16, dt * 32, lane), d, dq[dt]);
+      }
+    };
+    if (valid) {
+      scores(0);
+      grads(0);
+      scores(1);
     }
-    }
-    if (next) {
-      tk.store(Ks[grp][cur ^ 1], LDK, tid);
-      tv.store(Vs[grp][cur ^ 1], LDK, tid);
-    }
-    __syncthreads();
+    wait_vm<0>();
+    barrier();  // every wave has read V
+    cp.issue(V + (int64_t)cc * BQ * D, vc, p + NG < p1);
+    if (valid) grads(1);
+    wait_vm<4>();
+    barrier();  // every wave has read K
+    cp.issue(K + (int64_t)cc * BQ * D, kc, p + NG < p1);
   }
+  wait_vm<0>();  // no copy outlives the workgroup
 
   if constexpr (NG > 1) {
-    // Groups 1.. leave their 16 partial sums per lane in their K tiles;
-    // group 0 adds them in group order.
-    float *mrg = (float *)&Ks[grp][0][0] + wave * (16 * 64) + lane;
+    // Groups 1.. leave their 32 partial sums per lane in their tiles; group
+    // 0 adds them in group order.
+    barrier();
     if (grp > 0) {
+      float *m0 = merge_at(kst, grp, w, lane), *m1 = merge_at(vst, grp, w, lane);
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) mrg[(dt * 4 + j) * 64] = dq[dt][j];
+      for (int e = 0; e < 16; ++e) {
+        m0[e * 64] = dq[0][e];
+        m1[e * 64] = dq[1][e];
+      }
     }
     __syncthreads();
     if (grp > 0) return;
 #pragma unroll
     for (int g = 1; g < NG; ++g) {
-      const float *src = (const float *)&Ks[g][0][0] + wave * (16 * 64) + lane;
+      const float *m0 = merge_at(kst, g, w, lane), *m1 = merge_at(vst, g, w, lane);
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) dq[dt][j] += src[(dt * 4 + j) * 64];
+      for (int e = 0; e < 16; ++e) {
+        dq[0][e] += m0[e * 64];
+        dq[1][e] += m1[e * 64];
+      }
     }
   }
-
-  bf16_t *dQ = (bf16_t *)a.dQ + head + (int64_t)q * D;
-#pragma unroll
-  for (int dt = 0; dt < 4; ++dt) {
-    u32x2 w;
-    w[0] = (uint32_t)f2bf_a(dq[dt][0] * a.scale) | ((uint32_t)f2bf_a(dq[dt][1] * a.scale) << 16);
-    w[1] = (uint32_t)f2bf_a(dq[dt][2] * a.scale) | ((uint32_t)f2bf_a(dq[dt][3] * a.scale) << 16);
-    *(u32x2 *)(dQ + dt * 16 + (lane >> 4) * 4) = w;
-  }
+  store_row((bf16_t *)a.dQ + head + (int64_t)q * D, dq, a.scale, lane);
 }
 
 // ---------------------------------------------------------------------------
-// Backward, pass 2: dK and dV (one workgroup per key block)
+// Backward, pass 2: dK and dV (a group per key block)
 // ---------------------------------------------------------------------------
-// NG groups of 4 waves split the column's kept blocks as in the forward;
-// their dK and dV partial sums are added through LDS in group order.
+// NG groups split the column's kept blocks as in the forward; their dK and
+// dV partial sums are added through LDS in group order.
 template <int NG>
-__global__ __launch_bounds__(256 * NG) void attn_bwd_dkv_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) bf16_t Qs[NG][2][BQ * LDK];
-  __shared__ __attribute__((aligned(16))) bf16_t dOs[NG][2][BQ * LDK];
-  __shared__ float ls[NG][2][BQ], ds[NG][2][BQ];
+__global__ __launch_bounds__(128 * NG) void attn_bwd_dkv_kernel(AttnArgs a) {
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 1);
+  const int grp = NG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 7) : 0;
+  uint8_t *const qs0 = stage_buf<0, NG * TILE>(), *const ds0 = stage_buf<1, NG * TILE>();
+  uint8_t *const qs1 = stage_buf<2, NG * TILE>(), *const ds1 = stage_buf<3, NG * TILE>();
+  // Row terms of the 64 queries: lse (log2 units), then -delta.
+  __shared__ __attribute__((aligned(16))) float rt0[NG][2 * BQ], rt1[NG][2 * BQ];
 
-  const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;
-  const int grp = NG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) : 0;
-  const int bid = xcd_remap_a(blockIdx.x, gridDim.x) + a.first;
+  const int bid = xcd_remap(blockIdx.x, gridDim.x) + a.first;
   int bh, kb;
   attn_order(bid, a.BH, a.nbq, a.nlong, bh, kb);
   const int64_t head = (int64_t)bh * a.S * D;
@@ -479,133 +490,134 @@ __global__ __launch_bounds__(256 * NG) void attn_bwd_dkv_kernel(AttnArgs a) {
   const bf16_t *K = (const bf16_t *)a.K + head;
   const bf16_t *V = (const bf16_t *)a.V + head;
   const bf16_t *dO = (const bf16_t *)a.dO + head;
-  const float *lse = a.lse_in + (int64_t)bh * a.S;
-  const float *dl = a.delta + (int64_t)bh * a.S;
-  const int k0 = kb * BQ + wave * 16;
+  // Wave 0 of a group carries the lse values, wave 1 the delta values.
+  const float *rt_g = (w == 0 ? a.lse_in : a.delta) + (int64_t)bh * a.S;
+  const float rt_scale = w == 0 ? kLog2e : -1.f;
+  const int k0 = kb * BQ + w * 32;
   const float c = a.scale * kLog2e;
 
-  bf16x8 kf[2], vf[2];
-  kf[0] = frag_rows_g(K, k0, 0, lane);
-  kf[1] = frag_rows_g(K, k0, 32, lane);
-  vf[0] = frag_rows_g(V, k0, 0, lane);
-  vf[1] = frag_rows_g(V, k0, 32, lane);
-
-  const int p0 = a.col_ptr[kb], p1 = a.col_ptr[kb + 1];
-  f32x4 dk[4], dv[4];
+  const int p0 = ld_meta(a.col_ptr + kb), p1 = ld_meta(a.col_ptr + kb + 1);
+  f32x16 dk[2], dv[2];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    dk[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    dv[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+  for (int e = 0; e < 16; ++e) dk[0][e] = dk[1][e] = dv[0][e] = dv[1][e] = 0.f;
+
   if (p0 < p1) {  // a key block no query attends keeps zero gradients
-
-  Tile64 tq, td;
-  float rl = 0.f, rd = 0.f;
-  auto gload = [&](int p) {
-    const int64_t qrow = (int64_t)a.row_idx[p] * BQ;
-    tq.load(Q + qrow * D, tid);
-    td.load(dO + qrow * D, tid);
-    // Raw values: scaling here would make the wave wait for the load.
-    if (tid < BQ) { rl = lse[qrow + tid]; rd = dl[qrow + tid]; }
-  };
-  auto sstore = [&](int buf) {
-    tq.store(Qs[grp][buf], LDK, tid);
-    td.store(dOs[grp][buf], LDK, tid);
-    if (tid < BQ) { ls[grp][buf][tid] = rl * kLog2e; ds[grp][buf][tid] = rd; }
-  };
-  const int iters = (p1 - p0 + NG - 1) / NG;
-  if (p0 + grp < p1) {
-    gload(p0 + grp);
-    sstore(0);
-  }
-  __syncthreads();
-
-  for (int it = 0; it < iters; ++it) {
-    const int cur = it & 1;
-    const int p = p0 + it * NG + grp;
-    const bool valid = p < p1, next = p + NG < p1;
-    if (next) gload(p + NG);
-    if (valid) {
-    // S[query][key], dP[query][key] for 64 queries x this wave's 16 keys.
-    f32x4 s[4], dp[4];
+    const int iters = (p1 - p0 + NG - 1) / NG;
+    TileCopy cp;
+    cp.init(lane, w);
+    float rt = 0.f;  // raw row term of the block in flight
+    auto issue = [&](int row, uint8_t *qt, uint8_t *dt) __attribute__((always_inline)) {
+      cp.issue(Q + (int64_t)row * BQ * D, qt + grp * TILE, true);
+      cp.issue(dO + (int64_t)row * BQ * D, dt + grp * TILE, true);
+      rt = rt_g[row * BQ + lane];
+    };
+    if (p0 + grp < p1) issue(ld_meta(a.row_idx + p0 + grp), qs0, ds0);
+    bf16x8 kf[4], vf[4];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      s[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-      s[mt] = MFMA16(frag_rows(Qs[grp][cur], LDK, mt * 16, 0, lane), kf[0], s[mt]);
-      s[mt] = MFMA16(frag_rows(Qs[grp][cur], LDK, mt * 16, 32, lane), kf[1], s[mt]);
-      dp[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-      dp[mt] = MFMA16(frag_rows(dOs[grp][cur], LDK, mt * 16, 0, lane), vf[0], dp[mt]);
-      dp[mt] = MFMA16(frag_rows(dOs[grp][cur], LDK, mt * 16, 32, lane), vf[1], dp[mt]);
+    for (int ks = 0; ks < 4; ++ks) {
+      kf[ks] = frag_g(K, k0, ks, lane);
+      vf[ks] = frag_g(V, k0, ks, lane);
     }
+    int rn = ld_meta(a.row_idx + min(p0 + grp + NG, p1 - 1));
+
+    auto step = [&](int it, uint8_t *qc, uint8_t *dc, float (&rc)[NG][2 * BQ], uint8_t *qn,
+                    uint8_t *dn) __attribute__((always_inline)) {
+      const int p = p0 + it * NG + grp;
+      wait_vm<0>();
+      // The stage's row terms were last read two blocks ago, before the
+      // previous barrier.
+      rc[grp][w * BQ + lane] = rt * rt_scale;
+      wait_vm<0>();
+      barrier();
+      if (p + NG < p1) issue(rn, qn, dn);
+      rn = ld_meta(a.row_idx + min(p + 2 * NG, p1 - 1));
+      if (p >= p1) return;
+      qc += grp * TILE;
+      dc += grp * TILE;
+      const float *lsep = &rc[grp][(lane >> 5) * 4], *delp = lsep + BQ;
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+      for (int qt = 0; qt < 2; ++qt) {
+        // S[query][key], dP[query][key] for 32 queries x this wave's 32 keys.
+        // The accumulators of dP start at -delta.
+        f32x16 s = {}, dp;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int qi = mt * 16 + (lane >> 4) * 4 + j;
-        const float pr = fast_exp2(s[mt][j] * c - ls[grp][cur][qi]);
-        s[mt][j] = pr;
-        dp[mt][j] = pr * (dp[mt][j] - ds[grp][cur][qi]);  // dS
+        for (int e4 = 0; e4 < 4; ++e4) {
+          const f32x4 de = *(const f32x4 *)(delp + qt * 32 + e4 * 8);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) dp[e4 * 4 + j] = de[j];
+        }
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+          s = MFMA32(frag_r(qc, qt * 32, ks, lane), kf[ks], s);
+          dp = MFMA32(frag_r(dc, qt * 32, ks, lane), vf[ks], dp);
+        }
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4) {
+          const f32x4 ls = *(const f32x4 *)(lsep + qt * 32 + e4 * 8);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int e = e4 * 4 + j;
+            const float pr = fast_exp2(s[e] * c - ls[j]);
+            s[e] = pr;
+            dp[e] = pr * dp[e];  // dS
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const bf16x8 pb = pack_k(s, j), sb = pack_k(dp, j);
+#pragma unroll
+          for (int dt = 0; dt < 2; ++dt) {
+            dv[dt] = MFMA32(frag_t(dc, qt * 32 + j * 16, dt * 32, lane), pb, dv[dt]);
+            dk[dt] = MFMA32(frag_t(qc, qt * 32 + j * 16, dt * 32, lane), sb, dk[dt]);
+          }
+        }
       }
-    const bf16x8 pb0 = pack_perm(s[0], s[1]), pb1 = pack_perm(s[2], s[3]);
-    const bf16x8 sb0 = pack_perm(dp[0], dp[1]), sb1 = pack_perm(dp[2], dp[3]);
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) {
-      dv[dt] = MFMA16(fragA_tr_perm(dOs[grp][cur], LDK, 0, dt * 16, lane), pb0, dv[dt]);
-      dv[dt] = MFMA16(fragA_tr_perm(dOs[grp][cur], LDK, 32, dt * 16, lane), pb1, dv[dt]);
-      dk[dt] = MFMA16(fragA_tr_perm(Qs[grp][cur], LDK, 0, dt * 16, lane), sb0, dk[dt]);
-      dk[dt] = MFMA16(fragA_tr_perm(Qs[grp][cur], LDK, 32, dt * 16, lane), sb1, dk[dt]);
+    };
+    for (int it = 0; it < iters; it += 2) {
+      step(it, qs0, ds0, rt0, qs1, ds1);
+      if (it + 1 < iters) step(it + 1, qs1, ds1, rt1, qs0, ds0);
     }
-    }
-    if (next) sstore(cur ^ 1);
-    __syncthreads();
-  }
   }
 
   if constexpr (NG > 1) {
-    // Groups 1.. leave their 32 partial sums per lane in their Q and dO
-    // tiles; group 0 adds them in group order.  (The key block's kept-block
-    // count is workgroup-uniform, so every thread reaches this barrier.)
-    float *mk = (float *)&Qs[grp][0][0] + wave * (16 * 64) + lane;
-    float *mv = (float *)&dOs[grp][0][0] + wave * (16 * 64) + lane;
+    // Groups 1.. leave their 64 partial sums per lane in their tiles; group
+    // 0 adds them in group order.  (The key block's kept-block count is
+    // workgroup-uniform, so every thread reaches these barriers.)
+    wait_vm<0>();
+    barrier();
     if (grp > 0) {
+      float *m0 = merge_at(qs0, grp, w, lane), *m1 = merge_at(ds0, grp, w, lane);
+      float *m2 = merge_at(qs1, grp, w, lane), *m3 = merge_at(ds1, grp, w, lane);
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          mk[(dt * 4 + j) * 64] = dk[dt][j];
-          mv[(dt * 4 + j) * 64] = dv[dt][j];
-        }
+      for (int e = 0; e < 16; ++e) {
+        m0[e * 64] = dk[0][e];
+        m1[e * 64] = dk[1][e];
+        m2[e * 64] = dv[0][e];
+        m3[e * 64] = dv[1][e];
+      }
     }
     __syncthreads();
     if (grp > 0) return;
 #pragma unroll
     for (int g = 1; g < NG; ++g) {
-      const float *sk = (const float *)&Qs[g][0][0] + wave * (16 * 64) + lane;
-      const float *sv = (const float *)&dOs[g][0][0] + wave * (16 * 64) + lane;
+      const float *m0 = merge_at(qs0, g, w, lane), *m1 = merge_at(ds0, g, w, lane);
+      const float *m2 = merge_at(qs1, g, w, lane), *m3 = merge_at(ds1, g, w, lane);
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          dk[dt][j] += sk[(dt * 4 + j) * 64];
-          dv[dt][j] += sv[(dt * 4 + j) * 64];
-        }
+      for (int e = 0; e < 16; ++e) {
+        dk[0][e] += m0[e * 64];
+        dk[1][e] += m1[e * 64];
+        dv[0][e] += m2[e * 64];
+        dv[1][e] += m3[e * 64];
+      }
     }
   }
 
-  const int key = k0 + (lane & 15);
-  bf16_t *dK = (bf16_t *)a.dK + head + (int64_t)key * D;
-  bf16_t *dV = (bf16_t *)a.dV + head + (int64_t)key * D;
-#pragma unroll
-  for (int dt = 0; dt < 4; ++dt) {
-    u32x2 w;
-    w[0] = (uint32_t)f2bf_a(dk[dt][0] * a.scale) | ((uint32_t)f2bf_a(dk[dt][1] * a.scale) << 16);
-    w[1] = (uint32_t)f2bf_a(dk[dt][2] * a.scale) | ((uint32_t)f2bf_a(dk[dt][3] * a.scale) << 16);
-    *(u32x2 *)(dK + dt * 16 + (lane >> 4) * 4) = w;
-    w[0] = (uint32_t)f2bf_a(dv[dt][0]) | ((uint32_t)f2bf_a(dv[dt][1]) << 16);
-    w[1] = (uint32_t)f2bf_a(dv[dt][2]) | ((uint32_t)f2bf_a(dv[dt][3]) << 16);
-    *(u32x2 *)(dV + dt * 16 + (lane >> 4) * 4) = w;
-  }
+  const int64_t key = k0 + (lane & 31);
+  store_row((bf16_t *)a.dK + head + key * D, dk, a.scale, lane);
+  store_row((bf16_t *)a.dV + head + key * D, dv, 1.f, lane);
 }
+
+}  // namespace
 
 // Launchers.  part 0: every block row (column) with the plain kernel;
 // part 1: the nlong global rows (columns) of every head with the grouped
@@ -626,23 +638,23 @@ hipError_t attn_launch(F1 plain, FG grouped, int ng, AttnArgs a, int part, hipSt
   }
   if (grid <= 0 || grid > 0x7fffffff) return hipErrorInvalidValue;
   if (part == 1)
-    launch_kernel(grouped, dim3((unsigned)grid), dim3(256 * ng), s, a);
+    launch_kernel(grouped, dim3((unsigned)grid), dim3(128 * ng), s, a);
   else
-    launch_kernel(plain, dim3((unsigned)grid), dim3(256), s, a);
+    launch_kernel(plain, dim3((unsigned)grid), dim3(128), s, a);
   return hipGetLastError();
 }
 }  // namespace
 
 hipError_t launch_attn_fwd(const AttnArgs &a, int part, hipStream_t s) {
-  return attn_launch(attn_fwd_kernel<1>, attn_fwd_kernel<4>, 4, a, part, s);
+  return attn_launch(attn_fwd_kernel<1>, attn_fwd_kernel<8>, 8, a, part, s);
 }
 
 hipError_t launch_attn_bwd_dq(const AttnArgs &a, int part, hipStream_t s) {
-  return attn_launch(attn_bwd_dq_kernel<1>, attn_bwd_dq_kernel<4>, 4, a, part, s);
+  return attn_launch(attn_bwd_dq_kernel<1>, attn_bwd_dq_kernel<8>, 8, a, part, s);
 }
 
 hipError_t launch_attn_bwd_dkv(const AttnArgs &a, int part, hipStream_t s) {
-  return attn_launch(attn_bwd_dkv_kernel<1>, attn_bwd_dkv_kernel<2>, 2, a, part, s);
+  return attn_launch(attn_bwd_dkv_kernel<1>, attn_bwd_dkv_kernel<4>, 4, a, part, s);
 }
 
 // Scratch of the allocation-free attention backward: the row terms delta,

@@ -135,3 +135,51 @@ def test_attention_repeat_calls_bitwise():
     for r in runs[1:]:
         for name in runs[0]:
             assert torch.equal(r[name], runs[0][name]), name
+
+
+@pytest.mark.parametrize("order", ["growing", "shrinking"])
+def test_attention_moving_reference_and_empty_columns(order):
+    """Scores that grow (shrink) from key block to key block by far more than
+    the forward's rescale threshold, in both halves of a block, on a mask with
+    rows of 1 .. 5 blocks (odd and even counts of the double-buffered loops)
+    and one key block that no query attends (zero dK, dV)."""
+    torch = torch_cuda()
+    from paper_2112_00029_amd import pixelfly as pf
+    B, H, nb, d, b = 1, 2, 6, 64, 64
+    S = nb * b
+    print(f"[attn-moving] {order}", flush=True)
+    mask = np.array([[1, 0, 0, 0, 0, 0], [1, 1, 0, 0, 0, 0], [1, 0, 1, 0, 1, 0],
+                     [1, 1, 1, 1, 0, 0], [1, 1, 1, 1, 1, 0], [0, 0, 0, 0, 1, 0]], np.uint8)
+    raw = {n: synth.draw((B, H, S, d), 1.0, 9, sid, "bf16") for n, sid in
+           (("Q", 11), ("K", 12), ("V", 13), ("dO", 14))}
+    # Powers of two per 32 keys (exact in bf16), 1/4 .. 4: scores of 4 x N(0, 1),
+    # a maximum near 8 (11 in log2 units, past the threshold of 8).
+    g = 2.0 ** (np.arange(2 * nb) // 2 - 2 + (np.arange(2 * nb) % 2))
+    g = np.minimum(g if order == "growing" else g[::-1], 4.0).repeat(32)[:, None]
+    K = raw["K"][0] * g
+    Kr = synth.bf16_bits_from_f32(K.astype(np.float32))
+    L = pf.pf_layout_create_from_mask(nb, nb, b, mask)
+    pf.pf_layout_upload(L)
+    q, k, v, do = to_dev(raw["Q"][1]), to_dev(Kr), to_dev(raw["V"][1]), to_dev(raw["dO"][1])
+    O, dQ, dK, dV = (empty((B, H, S, d), "bf16") for _ in range(4))
+    lse = torch.empty((B, H, S), dtype=torch.float32, device="cuda")
+    pf.pf_attn_fwd(L, B, H, S, d, 0.125, q, k, v, O, lse)
+    wsb = pf.pf_attn_workspace_bytes(B, H, S)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    pf.pf_attn_bwd(L, B, H, S, d, 0.125, q, k, v, O, lse, do, dQ, dK, dV, ws, wsb)
+    torch.cuda.synchronize()
+    assert not to_host(dK)[:, :, 5 * b:].any() and not to_host(dV)[:, :, 5 * b:].any()
+    Mel = om.element_mask(mask.astype(bool), b)
+    for h in range(H):
+        Qh, Kh, Vh, dOh = raw["Q"][0][0, h], K[0, h], raw["V"][0][0, h], raw["dO"][0][0, h]
+        o, l, _ = oa.forward_head(Qh, Kh, Vh, Mel, 0.125)
+        # Reference gradients of the backward call's own inputs, O and lse as
+        # the forward stored them: where a row is nearly one-hot, dP - delta
+        # cancels, and the rounding of O would weigh more than the kernel.
+        Oh, lh = to_host(O)[0, h], lse.cpu().numpy().astype(np.float64)[0, h]
+        P = np.where(Mel, np.exp(Qh @ Kh.T * 0.125 - lh[:, None]), 0.0)
+        dS = P * (dOh @ Vh.T - (dOh * Oh).sum(1)[:, None])
+        for n, got, ref in (("O", O, o), ("dQ", dQ, dS @ Kh * 0.125), ("dK", dK, dS.T @ Qh * 0.125),
+                            ("dV", dV, P.T @ dOh)):
+            check_close(n, to_host(got)[0, h], ref, "bf16", row_floor=1.0)
+        check_close("lse", lh, l, "bf16", row_floor=1.0)
