@@ -114,3 +114,13 @@ def test_product_kernel(n, ms, T):
         row_ptr, col_idx, *_r = om.block_csr(Sb)
         check_close(f"dF_{f + 1}", D[f * 2 * nb:(f + 1) * 2 * nb],
                     ol.pack(dFr[f], row_ptr, col_idx, nb, b), "bf16")
+
+
+@pytest.mark.parametrize("n,ms,T", [(960, 2, 17),   # last workgroup of a row: 6 of 8 blocks
+                                    (64, 2, 1),     # fewer blocks than a workgroup takes, one token
+                                    (384, 4, 16),   # 12 blocks: 8 + 4
+                                    (1536, 16, 31), (3072, 32, 15)])
+def test_product_kernel_partial_tiles(n, ms, T):
+    """Block counts that do not fill the workgroups' block sets, token counts
+    around the 16-token tile, and several groups per token tile."""
+    test_product_kernel(n, ms, T)
