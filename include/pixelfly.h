@@ -246,7 +246,7 @@ pf_status pf_layout_plan_get(const pf_layout *layout, int32_t *stats,
  * Diagnostic: the kernels and work split a forward + backward step of T
  * tokens at rank r runs on this layout (host only; the layout need not be
  * uploaded).  The rank-r products T_lr = X V^T and S = dY U report kernel 0
- * (r = 0, not run), 1 (the rank-r kernel: 32-token x 64-column workgroups)
+ * (r = 0, not run), 1 (the rank-r kernel, no split over workgroups)
  * or 2 (the tile kernel in dense mode), the number of workgroups that split
  * one output tile's K range (fp32 partials summed by a second pass when
  * above 1) and the output tile (tokens x columns).  The block-sparse

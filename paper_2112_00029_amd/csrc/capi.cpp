@@ -228,28 +228,37 @@ pf_status dense_nt(pf_kernel_class kc, int dtype, int blk, int G, bool b_kn, int
   return hip_status(pf::launch_reduce_rows(dtype, nsplit, ws, M, (int64_t)nblk * blk, C, ldc, s), what);
 }
 
-// The bf16 rank-r kernel (32-token x 64-column workgroups, no split) runs a
-// product when 128 x 128 tiles would cover less than a quarter of the CUs
-// (those then need a deep K split, fp32 partials and a reduction pass).
-// With more tiles the tile kernel re-reads the small operand far less and
-// measured faster (4096 tokens, r = 96: rank-r kernel; 8192 tokens,
-// r = 128: tiles).
-// Rank-r products go to the rank-r kernel while 128 x 128 tiles would cover
-// fewer than PF_SKINNY_MAX_TILES of them (a quarter of the CUs).
+// The bf16 rank-r kernel (one launch, no split over workgroups) or the tile
+// kernel (128 x 128 or 256 x 256 tiles, a K split with fp32 partials and a
+// reduction pass).  The rank-r kernel runs a product while 128 x 128 tiles
+// would cover fewer than PF_SKINNY_MAX_TILES of them (a quarter of the CUs)
+// and its busiest compute unit reads at most kSkinnyBytes, about 28 us of
+// operand bytes (skinny_tile): with few token rows every workgroup reads
+// the whole second operand, and for deep products the split, whose tiles
+// share it, wins despite its two passes (2509 x 16384 to r = 256: 4.2 MB, 49
+// us against 35 + 5; 2509 x 4096: 1 MB, 13.9 us against 15.3 + 5).
+// S = dY U keeps the rank-r kernel one tile further for K up to 2048 (8192 x
+// 1024 to r = 128: 8.1 us against 9.9 + 5.4).
 #ifndef PF_SKINNY_MAX_TILES
 #define PF_SKINNY_MAX_TILES 64
 #endif
-// The rank-r kernel addresses its operands through 32-bit buffer ranges and
-// points steps past the end at the offset 0x7ffffff0, which must lie outside
-// every range: A's 32-row tile (32 K-long rows) and the whole r x K (or
-// K x r) second operand.  Larger shapes take the tile kernel.
+constexpr int64_t kSkinnyBytes = 5 << 19;
+// It addresses its operands through 32-bit buffer ranges and points what
+// lies past the end at the offset 0x7ffffff0, which must lie outside every
+// range: A's tile (64 K-long rows) and the whole r x K (or K x r) second
+// operand.  Larger shapes take the tile kernel.
 bool skinny_fits(int64_t K, int r) {
   const int64_t lim = 0x7ffffff0LL;
-  return 32 * K * 2 < lim && (int64_t)r * K * 2 < lim;
+  return 64 * K * 2 < lim && (int64_t)r * K * 2 < lim;
 }
-bool use_skinny(int dtype, int64_t T, int r, int64_t K) {
-  return dtype == 0 && r > 0 && ((T + 127) / 128) * ((r + 127) / 128) < PF_SKINNY_MAX_TILES &&
-         skinny_fits(K, r);
+bool skinny_small(int dtype, int64_t T, int r, int64_t K, bool s_side) {
+  if (dtype != 0 || r <= 0 || !skinny_fits(K, r)) return false;
+  const int64_t tiles = ((T + 127) / 128) * ((r + 127) / 128);
+  return tiles < PF_SKINNY_MAX_TILES + (s_side && K <= 2048 ? 1 : 0);
+}
+bool use_skinny(int dtype, int64_t T, int r, int64_t K, bool s_side) {
+  return skinny_small(dtype, T, r, K, s_side) &&
+         pf::skinny_tile(s_side, T, r).cost * 2 * K <= kSkinnyBytes;
 }
 
 // bf16 rank-r product C[M x r] = A[M x K] . op(B) on the rank-r kernel
@@ -285,15 +294,16 @@ struct SkinnyPlan {
   size_t ws;
   int G;  // output blocks per tile (128 or 256 columns)
   int blk = 0;  // block width of the product's K-steps and output blocks
+  bool skinny = false;  // the rank-r kernel (set by rank_plan_ws)
 };
-SkinnyPlan skinny_plan(int dtype, int blk, int64_t T, int kblocks, int r) {
+SkinnyPlan skinny_plan(int dtype, int blk, int64_t T, int kblocks, int r, bool s_side) {
   SkinnyPlan p{dtype == 0 ? 128 : 64, 1, 0, 128 / blk};
   if (dtype != 0 && r > 0 && r < 128) {
     // fp32, r below one 128-column tile: one block per tile (no dead columns).
     p.G = 1;
     p.bm = blk == 32 ? 128 : 64;
   }
-  if (r <= 0 || use_skinny(dtype, T, r, (int64_t)kblocks * blk)) return p;  // no split
+  if (r <= 0 || use_skinny(dtype, T, r, (int64_t)kblocks * blk, s_side)) return p;  // no split
   if (dtype == 0 && r % 256 == 0 && T >= 2048 && (int64_t)kblocks * blk >= 8192) {
     // Deep products (S = dY U of a wide layer): 256 x 256 tiles, eight
     // waves, one workgroup per CU, split until about 256 workgroups run, at
@@ -349,8 +359,25 @@ int rank_blk(const pf_layout *L, int dtype, int32_t r, int64_t K) {
 SkinnyPlan rank_plan(const pf_layout *L, int dtype, int64_t T, int32_t r, bool s_side) {
   const int64_t K = s_side ? L->n_out : L->n_in;
   const int rb = rank_blk(L, dtype, r, K);
-  SkinnyPlan p = skinny_plan(dtype, rb, T, (int)(K / rb), r);
+  SkinnyPlan p = skinny_plan(dtype, rb, T, (int)(K / rb), r, s_side);
   p.blk = rb;
+  return p;
+}
+
+// Plan of a rank-r product for the workspace at hand: a product of few
+// tiles whose split does not fit into ws_bytes (less `extra`, the room its
+// call needs besides) runs on the rank-r kernel, which needs none.
+SkinnyPlan rank_plan_ws(const pf_layout *L, int dtype, int64_t T, int32_t r, bool s_side,
+                        size_t ws_bytes, size_t extra) {
+  SkinnyPlan p = rank_plan(L, dtype, T, r, s_side);
+  const int64_t K = s_side ? L->n_out : L->n_in;
+  p.skinny = use_skinny(dtype, T, r, K, s_side);
+  if (p.ws > 0 && ws_bytes < (extra ? (p.ws + 255) / 256 * 256 + extra : p.ws) &&
+      skinny_small(dtype, T, r, K, s_side)) {
+    p.skinny = true;
+    p.nsplit = 1;
+    p.ws = 0;
+  }
   return p;
 }
 
@@ -964,11 +991,12 @@ pf_status pf_linear_plan_get(const pf_layout *L, pf_dtype dtype, int64_t T, int3
   auto rank = [&](int64_t K, int kblocks, bool b_kn, int32_t *v) {
     (void)kblocks;
     if (r <= 0) return;
-    if (use_skinny(dt, T, r, K)) {
+    if (use_skinny(dt, T, r, K, b_kn)) {
+      const pf::SkinnyTile tile = pf::skinny_tile(b_kn, T, r);
       v[0] = 1;
       v[1] = 1;
-      v[2] = 32;
-      v[3] = 64;
+      v[2] = tile.m;
+      v[3] = tile.n;
       return;
     }
     const SkinnyPlan sp = rank_plan(L, dt, T, r, b_kn);
@@ -1074,12 +1102,12 @@ pf_status linear_fwd(const pf_layout *L, pf_dtype dtype, int64_t T, int32_t r, c
   if (epi != PF_EPI_NONE && epi != PF_EPI_GELU) return fail(PF_ERR_INVALID_ARG, "bad epilogue");
   if (epi == PF_EPI_GELU && (st = need_ptr(Y_pre, "Y_pre")) != PF_OK) return st;
   if (epi == PF_EPI_NONE && Y_pre) return fail(PF_ERR_INVALID_ARG, "Y_pre given without GELU epilogue");
-  const SkinnyPlan sp = rank_plan(L, (int)dtype, T, r, false);
+  const SkinnyPlan sp = rank_plan_ws(L, (int)dtype, T, r, false, ws_bytes, 0);
   if ((st = need_ws(sp.ws, workspace, ws_bytes)) != PF_OK) return st;
   if ((st = check_state(L)) != PF_OK) return st;
   hipStream_t s = (hipStream_t)stream;
   const int dt = (int)dtype, b = L->b;
-  if (use_skinny(dt, T, r, L->n_in)) {
+  if (sp.skinny) {
     st = skinny_bf16(PF_KERNEL_LOWRANK_T, false, T, X, L->n_in, V, L->n_in, (int)L->n_in, r, T_lr,
                      s, "T_lr kernel");
     if (st != PF_OK) return st;
@@ -1175,7 +1203,7 @@ pf_status check_bwd_weight_args(const pf_layout *L, pf_dtype dtype, int64_t T, i
 pf_status enqueue_s(const pf_layout *L, int dt, int64_t T, int32_t r, const void *dY,
                     const void *U, void *S, const SkinnyPlan &sp, float *ws, hipStream_t s) {
   if (r <= 0) return PF_OK;
-  if (use_skinny(dt, T, r, L->n_out))
+  if (sp.skinny)
     return skinny_bf16(PF_KERNEL_LOWRANK_S, true, T, dY, L->n_out, U, r, (int)L->n_out, r, S, s,
                        "S kernel");
   const int rb = sp.blk;
@@ -1378,8 +1406,8 @@ pf_status pf_linear_bwd_data(const pf_layout *L, pf_dtype dtype, int64_t T, int3
                              void *workspace, size_t ws_bytes, void *stream) {
   pf_status st = check_bwd_data_args(L, dtype, T, r, dY, Wblk, U, V, S, dX, epi, aux);
   if (st != PF_OK) return st;
-  const SkinnyPlan sp = rank_plan(L, (int)dtype, T, r, true);
   const size_t pws = pair_ws_bytes(L, (int)dtype, T, r);
+  const SkinnyPlan sp = rank_plan_ws(L, (int)dtype, T, r, true, ws_bytes, pws);
   if ((st = need_ws(pws ? align256(sp.ws) + pws : sp.ws, workspace, ws_bytes)) != PF_OK) return st;
   if ((st = check_state(L)) != PF_OK) return st;
   hipStream_t s = (hipStream_t)stream;
@@ -1409,8 +1437,8 @@ pf_status pf_linear_bwd_data_mixed(const pf_layout *L, pf_dtype dtype, int64_t T
   pf_status st = check_gamma(gamma);
   if (st != PF_OK) return st;
   if ((st = check_bwd_data_args(L, dtype, T, r, dY, Wblk, U, V, S, dX, epi, aux)) != PF_OK) return st;
-  const SkinnyPlan sp = rank_plan(L, (int)dtype, T, r, true);
   const size_t pws = pair_ws_bytes(L, (int)dtype, T, r);
+  const SkinnyPlan sp = rank_plan_ws(L, (int)dtype, T, r, true, ws_bytes, pws);
   if ((st = need_ws(pws ? align256(sp.ws) + pws : sp.ws, workspace, ws_bytes)) != PF_OK) return st;
   if ((st = check_state(L)) != PF_OK) return st;
   hipStream_t s = (hipStream_t)stream;

@@ -225,6 +225,29 @@ extern template hipError_t launch_tn_reduce_t<float>(int, const TNArgs &, hipStr
 // Work items of a TN launch on tile x tile tiles (128 or 256).
 int tn_items_total(const TNArgs &a, int blk, int tile = 128);
 hipError_t launch_skinny(bool b_kn, const SkinnyArgs &a, hipStream_t s);
+// Output tile of the rank-r kernel: the one whose busiest compute unit (256
+// of them, a workgroup each at a time) reads the fewest operand bytes,
+// rounds x (m + n) rows of K; on ties the larger tile, and 64 x 32 for
+// B [n][k], 32 x 64 for B [k][n], whose rows of 32 columns are half a cache
+// line (2100 x 4096 to r = 128: 13.1 against 16.5 us).  A compute unit takes
+// in about 88 bytes per ns however many copies are in flight, so that sum is
+// the time: 2509 x 4096 to r = 256 takes 13.9 us on 64 x 64 tiles, 21.4 on
+// 32 x 64; 4096 x 3072 to r = 96 13.1 us on 32 x 64, 15.1 on 64 x 64.
+struct SkinnyTile {
+  int m, n;
+  int64_t cost;  // rounds x (m + n): times 2 K, the bytes of the busiest unit
+};
+inline SkinnyTile skinny_tile(bool b_kn, int64_t M, int ncols) {
+  SkinnyTile best{0, 0, 0};
+  const int w = b_kn ? 32 : 64;
+  const int cand[4][2] = {{64, 64}, {w, 96 - w}, {96 - w, w}, {32, 32}};
+  for (const auto &c : cand) {
+    const int64_t wg = ((M + c[0] - 1) / c[0]) * ((ncols + c[1] - 1) / c[1]);
+    const int64_t cost = (wg + 255) / 256 * (c[0] + c[1]);
+    if (!best.m || cost < best.cost) best = SkinnyTile{c[0], c[1], cost};
+  }
+  return best;
+}
 // dgamma of the mixing weight: partial sums of <S, T_lr> (n elements,
 // kMixDotParts workgroups), then one workgroup adds the kernel-stored partial
 // dot products wparts[0 .. nw) and subtracts the S.T_lr partials, in a fixed

@@ -427,3 +427,48 @@ def test_large_layer_full_size_sampled(large_full_inputs, b):
     lr = ol.lowrank_grads(X, dY, U, V)
     for k in ("S", "dU", "dV"):
         check_close(k, to_host(out[k]), lr[k], "bf16")
+
+
+@pytest.mark.parametrize("T,n_in,n_out,r,t_tile,s_tile", [
+    (33, 480, 160, 32, (32, 32), (32, 32)),      # K and N = 32 mod 64, one row past a tile
+    (100, 3104, 3136, 96, (32, 32), (32, 32)),   # deep: eight waves, dead steps for some
+    (4090, 416, 3104, 96, (64, 32), (32, 64)),   # half a column tile past r (S)
+    (2500, 160, 288, 256, (64, 64), (64, 64)),   # fewer steps than waves
+])
+def test_rank_kernel_tiles(T, n_in, n_out, r, t_tile, s_tile):
+    """T_lr and S of the rank-r kernel on each of its tiles, in the short and
+    the deep wave split, at ragged token, K and rank edges."""
+    inp = _inputs(n_out, n_in, 32, 1, T, r, "bf16")
+    got, L = _run_gpu(n_out, n_in, 32, 1, T, r, "bf16", inp)
+    from paper_2112_00029_amd import pixelfly as pf
+    plan = pf.pf_linear_plan_get(L, "bf16", T, r)
+    assert (plan["lowrank_t_kernel"], plan["lowrank_s_kernel"]) == (1, 1), plan
+    assert (plan["lowrank_t_tile_m"], plan["lowrank_t_tile_n"]) == t_tile, plan
+    assert (plan["lowrank_s_tile_m"], plan["lowrank_s_tile_n"]) == s_tile, plan
+    ref = _oracle(inp, r, 32)
+    check_close("T_lr", got["T_lr"], ref["T_lr"], "bf16")
+    check_close("S", got["S"], ref["S"], "bf16")
+
+
+def test_deep_rank_product_without_workspace():
+    """S = dY U, 16384 deep at 2500 tokens and r = 256 (few tiles, split over K
+    by plan): given no workspace it runs on the rank-r kernel, and agrees with
+    the split."""
+    torch = torch_cuda()
+    from paper_2112_00029_amd import pixelfly as pf
+    T, n_in, n_out, r, b = 2500, 32, 16384, 256, 32
+    inp = _inputs(n_out, n_in, b, 1, T, r, "bf16")
+    L = pf.pf_layout_create(n_out, n_in, b, 1)
+    pf.pf_layout_upload(L)
+    plan = pf.pf_linear_plan_get(L, "bf16", T, r)
+    assert plan["lowrank_s_kernel"] == 2 and plan["lowrank_s_split"] > 1, plan
+    d = {k: to_dev(v) for k, v in inp["raw"].items()}
+    wsb = pf.pf_workspace_bytes(L, T, r, "bf16")
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    ref = _oracle(inp, r, b)["S"]
+    for w, n in ((ws, wsb), (None, 0)):
+        S, dX = empty((T, r), "bf16"), empty((T, n_in), "bf16")
+        pf.pf_linear_bwd_data(L, "bf16", T, r, d["dY"], d["W"], d["U"], d["V"], S, dX, workspace=w,
+                              ws_bytes=n)
+        torch.cuda.synchronize()
+        check_close("S", to_host(S), ref, "bf16")
