@@ -34,6 +34,7 @@
 #include <type_traits>
 
 #include "pf_dma.h"
+#include "pf_gelu.h"
 #include "pf_launch.h"
 
 // Token rows per group of the workgroup order (a group covers the token
@@ -49,13 +50,6 @@ namespace {
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)lo) |
          ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)hi) << 16);
-}
-__device__ __forceinline__ float gelu(float x) {
-  return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f));
-}
-__device__ __forceinline__ float gelu_grad(float x) {
-  const float Phi = 0.5f * (1.0f + erff(x * 0.70710678118654752f));
-  return Phi + x * 0.39894228040143268f * __expf(-0.5f * x * x);
 }
 
 template <int BLK, int G, bool BKN, int BM, int BK, int NS, int NW, bool DENSE, int EPI, int OCC>
@@ -456,8 +450,29 @@ __global__ __launch_bounds__(64 * NW, OCC) void ntd_kernel(NTArgs a_arg) {
     });
     return;
   }
-  sfor<TM * (32 / SP)>([&](auto pass) __attribute__((always_inline)) {
+  // GELU backward: the pre-activations of a pass are loaded one pass ahead.
+  // Loaded where they are used, each of the sixteen row groups of a 256 x
+  // 256 tile waited a memory round trip of its own (8192 x 4096: 80.5 ->
+  // 71 us).  Rows past M and dead columns read zero (range check), so the
+  // loads need no branch.
+  constexpr int NPASS = TM * (32 / SP), NIT = SP / RPI;
+  u32x4 ax[2][EPI == 2 ? NIT : 1];
+  const rsrc_t rx = make_rsrc(EPI == 2 ? (const bf16_t *)a.aux + m0 * a.ldc : nullptr,
+                              EPI == 2 ? (a.M - m0) * a.ldc * 2 : 0);
+  auto load_aux = [&](auto pass) __attribute__((always_inline)) {
+    if constexpr (EPI == 2 && decltype(pass)::value < NPASS) {
+      constexpr int tm = pass / (32 / SP), half = pass % (32 / SP);
+      sfor<NIT>([&](auto it) __attribute__((always_inline)) {
+        const uint32_t row = (uint32_t)(wm * WTM + tm * 32 + half * SP + it * RPI + rl);
+        const uint32_t off = col_ok ? (row * (uint32_t)a.ldc + (uint32_t)col) * 2u : 0x7ffffff0u;
+        ax[pass & 1][it] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)off, 0, 0);
+      });
+    }
+  };
+  load_aux(std::integral_constant<int, 0>{});
+  sfor<NPASS>([&](auto pass) __attribute__((always_inline)) {
     constexpr int tm = pass / (32 / SP), half = pass % (32 / SP);
+    load_aux(std::integral_constant<int, pass + 1>{});
     if ((lane & 31) / SP == half) {
       const int r = (lane & 31) % SP;
       sfor<TN>([&](auto tn) __attribute__((always_inline)) {
@@ -469,7 +484,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void ntd_kernel(NTArgs a_arg) {
         });
       });
     }
-    sfor<SP / RPI>([&](auto it) __attribute__((always_inline)) {
+    sfor<NIT>([&](auto it) __attribute__((always_inline)) {
       const int r = it * RPI + rl;
       const f32x4 lo = *(const f32x4 *)(stg + r * SROW + (((2 * jl) ^ (r & (SCH - 1))) << 4));
       const f32x4 hi = *(const f32x4 *)(stg + r * SROW + (((2 * jl + 1) ^ (r & (SCH - 1))) << 4));
@@ -491,13 +506,13 @@ __global__ __launch_bounds__(64 * NW, OCC) void ntd_kernel(NTArgs a_arg) {
         *(u32x4 *)((bf16_t *)a.C2 + o) = u32x4{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]),
                                                pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = gelu(v[e]);
+        for (int e = 0; e < 8; ++e) v[e] = gelu_fast(v[e]);
       } else if constexpr (EPI == 2) {  // backward GELU: scale by gelu'(pre-activation)
-        const u32x4 x = *(const u32x4 *)((const bf16_t *)a.aux + o);
+        const u32x4 x = ax[pass & 1][it];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          v[2 * e] *= gelu_grad(__uint_as_float(x[e] << 16));
-          v[2 * e + 1] *= gelu_grad(__uint_as_float(x[e] & 0xffff0000u));
+          v[2 * e] *= gelu_grad_fast(__uint_as_float(x[e] << 16));
+          v[2 * e + 1] *= gelu_grad_fast(__uint_as_float(x[e] & 0xffff0000u));
         }
       }
       *(u32x4 *)(C + o) = u32x4{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]),

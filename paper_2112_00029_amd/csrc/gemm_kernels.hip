@@ -31,6 +31,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "pf_gelu.h"
 #include "pf_launch.h"
 
 // Part of this file an object holds (see the launchers at the end).
@@ -72,6 +73,16 @@ __device__ __forceinline__ float gelu_grad_f(float x) {
   float Phi = 0.5f * (1.0f + erff(x * 0.70710678118654752f));
   float phi = 0.39894228040143268f * __expf(-0.5f * x * x);
   return Phi + x * phi;
+}
+
+// fp32 outputs keep the library erff; bf16 ones take the short form.
+template <typename T>
+__device__ __forceinline__ float gelu_t(float x) {
+  if constexpr (std::is_same<T, float>::value) return gelu_f(x); else return gelu_fast(x);
+}
+template <typename T>
+__device__ __forceinline__ float gelu_grad_t(float x) {
+  if constexpr (std::is_same<T, float>::value) return gelu_grad_f(x); else return gelu_grad_fast(x);
 }
 
 // Workgroups are dispatched round-robin over the 8 XCDs; remap so that
@@ -573,19 +584,19 @@ __global__ __launch_bounds__(256, 2) void nt_kernel(NTArgs a_arg) {
           *(f32x4 *)((T *)a.C2 + o + 4) = f32x4{v[4], v[5], v[6], v[7]};
         }
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = gelu_f(v[e]);
+        for (int e = 0; e < 8; ++e) v[e] = gelu_t<T>(v[e]);
       } else if constexpr (EPI == 2) {  // backward GELU: scale by gelu'(pre-activation)
         const T *ax = (const T *)a.aux + o;
         if constexpr (BF) {
           const u32x4 w = *(const u32x4 *)ax;
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            v[2 * e] *= gelu_grad_f(__uint_as_float(w[e] << 16));
-            v[2 * e + 1] *= gelu_grad_f(__uint_as_float(w[e] & 0xffff0000u));
+            v[2 * e] *= gelu_grad_t<T>(__uint_as_float(w[e] << 16));
+            v[2 * e + 1] *= gelu_grad_t<T>(__uint_as_float(w[e] & 0xffff0000u));
           }
         } else {
 #pragma unroll
-          for (int e = 0; e < 8; ++e) v[e] *= gelu_grad_f(ax[e]);
+          for (int e = 0; e < 8; ++e) v[e] *= gelu_grad_t<T>(ax[e]);
         }
       }
       if constexpr (BF) {
@@ -1008,7 +1019,7 @@ hipError_t launch_mix_dgamma(int dtype, const void *S, const void *T_lr, int64_t
 template <typename T>
 __global__ __launch_bounds__(256) void gelu_bwd_kernel(int64_t n, const T *dH, const T *Hpre, T *out) {
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-    out[i] = from_f<T>(to_f<T>(dH[i]) * gelu_grad_f(to_f<T>(Hpre[i])));
+    out[i] = from_f<T>(to_f<T>(dH[i]) * gelu_grad_t<T>(to_f<T>(Hpre[i])));
 }
 
 // ---------------------------------------------------------------------------
