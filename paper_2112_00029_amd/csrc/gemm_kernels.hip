@@ -631,10 +631,16 @@ __global__ __launch_bounds__(256) void reduce_rows_kernel(int nsplit, const floa
       for (int u = 0; u < 4; ++u)
         if (s0 + u < nsplit) v += t[u];
     }
-    const int64_t e = q * 4, row = e / ncols, col = e % ncols;
-    T *o = C + row * ldc + col;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] = from_f<T>(v[i]);
+    // Rows of C usually follow one another: no 64-bit division then, and
+    // one store of all four values (8192 x 128 from two splits: 9.2 -> 5.0 us).
+    int64_t o = q * 4;
+    if (ldc != ncols) o = o / ncols * ldc + o % ncols;
+    if constexpr (std::is_same<T, bf16_t>::value) {
+      *(uint2 *)(C + o) = uint2{(uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16),
+                                (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16)};
+    } else {
+      *(f32x4 *)(C + o) = v;
+    }
   }
 }
 
