@@ -180,14 +180,14 @@ __device__ __forceinline__ void attn_order(int L, int BH, int nb, int nlong, int
 // run the same number of iterations so every barrier is reached by the whole
 // workgroup) and the groups' softmax states (reference, sum, unnormalised O)
 // are merged through LDS in group order at the end.
-template <int NG>
-__global__ __launch_bounds__(128 * NG, NG == 1 ? 4 : 1) void attn_fwd_kernel(AttnArgs a) {
+template <int NG, int ST>
+__global__ __launch_bounds__(128 * NG, NG == 1 && ST == 1 ? 4 : 1) void attn_fwd_kernel(AttnArgs a) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 1);
   const int grp = NG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 7) : 0;
   uint8_t *const kst = stage_buf<0, NG * TILE>(), *const vst = stage_buf<1, NG * TILE>();
   __shared__ float ml[NG > 1 ? NG : 1][256];  // merge: reference and sum per lane
-  uint8_t *const kc = kst + grp * TILE, *const vc = vst + grp * TILE;
+  uint8_t *const k0s = kst + grp * TILE, *const v0s = vst + grp * TILE;
 
   const int bid = xcd_remap(blockIdx.x, gridDim.x) + a.first;
   int bh, qb;
@@ -206,7 +206,8 @@ __global__ __launch_bounds__(128 * NG, NG == 1 ? 4 : 1) void attn_fwd_kernel(Att
   TileCopy cp;
   cp.init(lane, w);
   int ccur = ld_meta(a.col_idx + min(p0 + grp, p1 - 1));
-  cp.issue(K + (int64_t)ccur * BQ * D, kc, p0 + grp < p1);
+  cp.issue(K + (int64_t)ccur * BQ * D, k0s, p0 + grp < p1);
+  if constexpr (ST == 2) cp.issue(V + (int64_t)ccur * BQ * D, v0s, p0 + grp < p1);
   bf16x8 qf[4];
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) qf[ks] = frag_g(Q, q0, ks, lane);
@@ -219,14 +220,9 @@ __global__ __launch_bounds__(128 * NG, NG == 1 ? 4 : 1) void attn_fwd_kernel(Att
 #pragma unroll
   for (int e = 0; e < 16; ++e) o[0][e] = o[1][e] = 0.f;
 
-  for (int it = 0; it < iters; ++it) {
-    const int p = p0 + it * NG + grp;
-    const bool valid = NG == 1 || p < p1;
-    wait_vm<0>();  // this wave's K copies have landed,
-    barrier();     // every wave's have, and the last block's V is read
-    cp.issue(V + (int64_t)ccur * BQ * D, vc, p < p1);
-    // S^T[key][query] for 64 keys x this wave's 32 queries.
-    f32x16 s[2];
+  f32x16 s[2];
+  // S^T[key][query] for 64 keys x this wave's 32 queries.
+  auto scores = [&](const uint8_t *kc) __attribute__((always_inline)) {
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt) {
 #pragma unroll
@@ -234,46 +230,40 @@ __global__ __launch_bounds__(128 * NG, NG == 1 ? 4 : 1) void attn_fwd_kernel(Att
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) s[kt] = MFMA32(frag_r(kc, kt * 32, ks, lane), qf[ks], s[kt]);
     }
-    wait_vm<4>();  // (no wait: the four V copies may be in flight)
-    barrier();     // every wave has read K
-    cp.issue(K + (int64_t)cn * BQ * D, kc, p + NG < p1);
-    ccur = cn;
-    cn = ld_meta(a.col_idx + min(p + 2 * NG, p1 - 1));
-    if (valid) {
-      float bmax = -INFINITY;
+  };
+  auto softmax = [&]() __attribute__((always_inline)) {
+    float bmax = -INFINITY;
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
+    for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) bmax = fmaxf(bmax, s[kt][e]);
-      // The softmax reference m_run (the same in both lanes of a query) moves
-      // only when some lane's maximum grew by more than 8 (log2 units): until
-      // then the probabilities stay below 2^8 and the rescale of O and l, a
-      // wave-uniform branch, is skipped.
-      if (__builtin_amdgcn_ballot_w64(fmaxf(m_run, bmax * c) > m_run + 8.0f)) {
-        const float m_cand = fmaxf(m_run, max_xor32(bmax) * c);
-        const float alpha = fast_exp2(m_run - m_cand);
-        m_run = m_cand;
-        l_run *= alpha;
+      for (int e = 0; e < 16; ++e) bmax = fmaxf(bmax, s[kt][e]);
+    // The softmax reference m_run (the same in both lanes of a query) moves
+    // only when some lane's maximum grew by more than 8 (log2 units): until
+    // then the probabilities stay below 2^8 and the rescale of O and l, a
+    // wave-uniform branch, is skipped.
+    if (__builtin_amdgcn_ballot_w64(fmaxf(m_run, bmax * c) > m_run + 8.0f)) {
+      const float m_cand = fmaxf(m_run, max_xor32(bmax) * c);
+      const float alpha = fast_exp2(m_run - m_cand);
+      m_run = m_cand;
+      l_run *= alpha;
 #pragma unroll
-        for (int dt = 0; dt < 2; ++dt)
+      for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-          for (int e = 0; e < 16; ++e) o[dt][e] *= alpha;
-      }
-      float rs = 0.f;
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const float x = fast_exp2(s[kt][e] * c - m_run);
-          s[kt][e] = x;
-          rs += x;
-        }
-      l_run += rs;
+        for (int e = 0; e < 16; ++e) o[dt][e] *= alpha;
     }
-    wait_vm<4>();  // V has landed; the next K copies stay in flight
-    barrier();
-    if (!valid) continue;
-    // O^T[dim][query] += V^T[dim][key] P^T[key][query]
+    float rs = 0.f;
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const float x = fast_exp2(s[kt][e] * c - m_run);
+        s[kt][e] = x;
+        rs += x;
+      }
+    l_run += rs;
+  };
+  // O^T[dim][query] += V^T[dim][key] P^T[key][query]
+  auto product = [&](const uint8_t *vc) __attribute__((always_inline)) {
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
@@ -283,6 +273,47 @@ __global__ __launch_bounds__(128 * NG, NG == 1 ? 4 : 1) void attn_fwd_kernel(Att
         for (int dt = 0; dt < 2; ++dt)
           o[dt] = MFMA32(frag_t(vc, kt * 32 + j * 16, dt * 32, lane), pb, o[dt]);
       }
+  };
+  if constexpr (ST == 1) {
+    for (int it = 0; it < iters; ++it) {
+      const int p = p0 + it * NG + grp;
+      const bool valid = NG == 1 || p < p1;
+      wait_vm<0>();  // this wave's K copies have landed,
+      barrier();     // every wave's have, and the last block's V is read
+      cp.issue(V + (int64_t)ccur * BQ * D, v0s, p < p1);
+      scores(k0s);
+      wait_vm<4>();  // (no wait: the four V copies may be in flight)
+      barrier();     // every wave has read K
+      cp.issue(K + (int64_t)cn * BQ * D, k0s, p + NG < p1);
+      ccur = cn;
+      cn = ld_meta(a.col_idx + min(p + 2 * NG, p1 - 1));
+      if (valid) softmax();
+      wait_vm<4>();  // V has landed; the next K copies stay in flight
+      barrier();
+      if (valid) product(v0s);
+    }
+  } else {
+    uint8_t *const k1s = stage_buf<2, NG * TILE>() + grp * TILE;
+    uint8_t *const v1s = stage_buf<3, NG * TILE>() + grp * TILE;
+    auto step = [&](int it, uint8_t *kc, uint8_t *vc, uint8_t *kn, uint8_t *vn)
+        __attribute__((always_inline)) {
+      const int p = p0 + it * NG + grp;
+      wait_vm<0>();  // this wave's copies of the block have landed,
+      barrier();     // every wave's have, and nobody reads the other stage
+      if (p + NG < p1) {
+        cp.issue(K + (int64_t)cn * BQ * D, kn, true);
+        cp.issue(V + (int64_t)cn * BQ * D, vn, true);
+      }
+      cn = ld_meta(a.col_idx + min(p + 2 * NG, p1 - 1));
+      if (NG > 1 && p >= p1) return;
+      scores(kc);
+      softmax();
+      product(vc);
+    };
+    for (int it = 0; it < iters; it += 2) {
+      step(it, k0s, v0s, k1s, v1s);
+      if (it + 1 < iters) step(it + 1, k1s, v1s, k0s, v0s);
+    }
   }
   wait_vm<0>();  // no copy outlives the workgroup
 
@@ -340,13 +371,13 @@ __global__ __launch_bounds__(128 * NG, NG == 1 ? 4 : 1) void attn_fwd_kernel(Att
 // ---------------------------------------------------------------------------
 // NG groups split the row's kept blocks as in the forward; their dQ partial
 // sums are added through LDS in group order.
-template <int NG>
-__global__ __launch_bounds__(128 * NG, NG == 1 ? 4 : 1) void attn_bwd_dq_kernel(AttnArgs a) {
+template <int NG, int ST>
+__global__ __launch_bounds__(128 * NG, NG == 1 && ST == 1 ? 4 : 1) void attn_bwd_dq_kernel(AttnArgs a) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 1);
   const int grp = NG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 7) : 0;
   uint8_t *const kst = stage_buf<0, NG * TILE>(), *const vst = stage_buf<1, NG * TILE>();
-  uint8_t *const kc = kst + grp * TILE, *const vc = vst + grp * TILE;
+  uint8_t *const k0s = kst + grp * TILE, *const v0s = vst + grp * TILE;
 
   const int bid = xcd_remap(blockIdx.x, gridDim.x) + a.first;
   int bh, qb;
@@ -366,8 +397,8 @@ __global__ __launch_bounds__(128 * NG, NG == 1 ? 4 : 1) void attn_bwd_dq_kernel(
   TileCopy cp;
   cp.init(lane, w);
   const int c0 = ld_meta(a.col_idx + min(p0 + grp, p1 - 1));
-  cp.issue(V + (int64_t)c0 * BQ * D, vc, p0 + grp < p1);
-  cp.issue(K + (int64_t)c0 * BQ * D, kc, p0 + grp < p1);
+  cp.issue(V + (int64_t)c0 * BQ * D, v0s, p0 + grp < p1);
+  cp.issue(K + (int64_t)c0 * BQ * D, k0s, p0 + grp < p1);
   bf16x8 qf[4], dof[4];
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
@@ -393,50 +424,76 @@ __global__ __launch_bounds__(128 * NG, NG == 1 ? 4 : 1) void attn_bwd_dq_kernel(
 #pragma unroll
   for (int e = 0; e < 16; ++e) dq[0][e] = dq[1][e] = 0.f;
 
-  for (int it = 0; it < iters; ++it) {
-    const int p = p0 + it * NG + grp;
-    const bool valid = NG == 1 || p < p1;
-    wait_vm<0>();  // this wave's copies of the block have landed,
-    barrier();     // every wave's have
-    const int cc = cn;
-    cn = ld_meta(a.col_idx + min(p + 2 * NG, p1 - 1));
-    // S^T and dP^T of 32 keys, dS^T from them, and its product with K.
-    f32x16 s, dp;
-    auto scores = [&](int kt) __attribute__((always_inline)) {
+  // S^T and dP^T of 32 keys, dS^T from them, and its product with K.
+  f32x16 s, dp;
+  auto scores = [&](const uint8_t *kc, const uint8_t *vc, int kt) __attribute__((always_inline)) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) s[e] = dp[e] = 0.f;
+    for (int e = 0; e < 16; ++e) s[e] = dp[e] = 0.f;
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        s = MFMA32(frag_r(kc, kt * 32, ks, lane), qf[ks], s);
-        dp = MFMA32(frag_r(vc, kt * 32, ks, lane), dof[ks], dp);
-      }
-    };
-    auto grads = [&](int kt) __attribute__((always_inline)) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float pr = fast_exp2(s[e] * c - lse2);
-        s[e] = pr * (dp[e] - delta);  // dS^T
-      }
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const bf16x8 d = pack_k(s, j);
-#pragma unroll
-        for (int dt = 0; dt < 2; ++dt)
-          dq[dt] = MFMA32(frag_t(kc, kt * 32 + j * 16, dt * 32, lane), d, dq[dt]);
-      }
-    };
-    if (valid) {
-      scores(0);
-      grads(0);
-      scores(1);
+    for (int ks = 0; ks < 4; ++ks) {
+      s = MFMA32(frag_r(kc, kt * 32, ks, lane), qf[ks], s);
+      dp = MFMA32(frag_r(vc, kt * 32, ks, lane), dof[ks], dp);
     }
-    wait_vm<0>();
-    barrier();  // every wave has read V
-    cp.issue(V + (int64_t)cc * BQ * D, vc, p + NG < p1);
-    if (valid) grads(1);
-    wait_vm<4>();
-    barrier();  // every wave has read K
-    cp.issue(K + (int64_t)cc * BQ * D, kc, p + NG < p1);
+  };
+  auto grads = [&](const uint8_t *kc, int kt) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const float pr = fast_exp2(s[e] * c - lse2);
+      s[e] = pr * (dp[e] - delta);  // dS^T
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const bf16x8 d = pack_k(s, j);
+#pragma unroll
+      for (int dt = 0; dt < 2; ++dt)
+        dq[dt] = MFMA32(frag_t(kc, kt * 32 + j * 16, dt * 32, lane), d, dq[dt]);
+    }
+  };
+  if constexpr (ST == 1) {
+    for (int it = 0; it < iters; ++it) {
+      const int p = p0 + it * NG + grp;
+      const bool valid = NG == 1 || p < p1;
+      wait_vm<0>();  // this wave's copies of the block have landed,
+      barrier();     // every wave's have
+      const int cc = cn;
+      cn = ld_meta(a.col_idx + min(p + 2 * NG, p1 - 1));
+      if (valid) {
+        scores(k0s, v0s, 0);
+        grads(k0s, 0);
+        scores(k0s, v0s, 1);
+      }
+      wait_vm<0>();
+      barrier();  // every wave has read V
+      cp.issue(V + (int64_t)cc * BQ * D, v0s, p + NG < p1);
+      if (valid) grads(k0s, 1);
+      wait_vm<4>();
+      barrier();  // every wave has read K
+      cp.issue(K + (int64_t)cc * BQ * D, k0s, p + NG < p1);
+    }
+  } else {
+    uint8_t *const k1s = stage_buf<2, NG * TILE>() + grp * TILE;
+    uint8_t *const v1s = stage_buf<3, NG * TILE>() + grp * TILE;
+    auto step = [&](int it, uint8_t *kc, uint8_t *vc, uint8_t *kn, uint8_t *vn)
+        __attribute__((always_inline)) {
+      const int p = p0 + it * NG + grp;
+      wait_vm<0>();
+      barrier();
+      if (p + NG < p1) {
+        cp.issue(K + (int64_t)cn * BQ * D, kn, true);
+        cp.issue(V + (int64_t)cn * BQ * D, vn, true);
+      }
+      cn = ld_meta(a.col_idx + min(p + 2 * NG, p1 - 1));
+      if (NG > 1 && p >= p1) return;
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt) {
+        scores(kc, vc, kt);
+        grads(kc, kt);
+      }
+    };
+    for (int it = 0; it < iters; it += 2) {
+      step(it, k0s, v0s, k1s, v1s);
+      if (it + 1 < iters) step(it + 1, k1s, v1s, k0s, v0s);
+    }
   }
   wait_vm<0>();  // no copy outlives the workgroup
 
@@ -622,9 +679,19 @@ __global__ __launch_bounds__(128 * NG) void attn_bwd_dkv_kernel(AttnArgs a) {
 // Launchers.  part 0: every block row (column) with the plain kernel;
 // part 1: the nlong global rows (columns) of every head with the grouped
 // kernel; part 2: the remaining rows with the plain kernel.
+//
+// `few` (two groups per block row, two stages per operand) is the plain kernel
+// of launches of at most two workgroups per CU: nothing else runs on the CU
+// then, and a row's serial chain of blocks is the time.  Rows of fewer than
+// four blocks on average do not repay the merge.  One group, one stage /
+// two groups, two stages (us): 12 heads x 1024, 5 blocks per row (192
+// workgroups), dQ 9.7 / 7.6; 24 heads (384) forward 8.3 / 7.7, dQ 11.7 /
+// 10.5; 48 heads (768) forward 9.6 / 11.6, dQ 13.5 / 15.1.
 namespace {
+constexpr int64_t kAttnFewWG = 512;
 template <typename F1, typename FG>
-hipError_t attn_launch(F1 plain, FG grouped, int ng, AttnArgs a, int part, hipStream_t s) {
+hipError_t attn_launch(F1 plain, F1 few, int nfew, FG grouped, int ng, AttnArgs a, int part,
+                       hipStream_t s) {
   int64_t grid;
   if (part == 1) {
     grid = (int64_t)a.BH * a.nlong;
@@ -639,6 +706,8 @@ hipError_t attn_launch(F1 plain, FG grouped, int ng, AttnArgs a, int part, hipSt
   if (grid <= 0 || grid > 0x7fffffff) return hipErrorInvalidValue;
   if (part == 1)
     launch_kernel(grouped, dim3((unsigned)grid), dim3(128 * ng), s, a);
+  else if (grid <= kAttnFewWG && a.nnzb >= 4 * (int64_t)a.nbq)
+    launch_kernel(few, dim3((unsigned)grid), dim3(128 * nfew), s, a);
   else
     launch_kernel(plain, dim3((unsigned)grid), dim3(128), s, a);
   return hipGetLastError();
@@ -646,15 +715,18 @@ hipError_t attn_launch(F1 plain, FG grouped, int ng, AttnArgs a, int part, hipSt
 }  // namespace
 
 hipError_t launch_attn_fwd(const AttnArgs &a, int part, hipStream_t s) {
-  return attn_launch(attn_fwd_kernel<1>, attn_fwd_kernel<8>, 8, a, part, s);
+  return attn_launch(attn_fwd_kernel<1, 1>, attn_fwd_kernel<2, 2>, 2, attn_fwd_kernel<8, 1>, 8, a,
+                     part, s);
 }
 
 hipError_t launch_attn_bwd_dq(const AttnArgs &a, int part, hipStream_t s) {
-  return attn_launch(attn_bwd_dq_kernel<1>, attn_bwd_dq_kernel<8>, 8, a, part, s);
+  return attn_launch(attn_bwd_dq_kernel<1, 1>, attn_bwd_dq_kernel<2, 2>, 2,
+                     attn_bwd_dq_kernel<8, 1>, 8, a, part, s);
 }
 
 hipError_t launch_attn_bwd_dkv(const AttnArgs &a, int part, hipStream_t s) {
-  return attn_launch(attn_bwd_dkv_kernel<1>, attn_bwd_dkv_kernel<4>, 4, a, part, s);
+  return attn_launch(attn_bwd_dkv_kernel<1>, attn_bwd_dkv_kernel<1>, 1, attn_bwd_dkv_kernel<4>, 4,
+                     a, part, s);
 }
 
 // Scratch of the allocation-free attention backward: the row terms delta,

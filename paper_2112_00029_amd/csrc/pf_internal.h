@@ -150,6 +150,7 @@ struct AttnArgs {
   float *delta;
   int BH, S, nbq;
   int nlong;            // leading block rows / columns kept whole (global stripes)
+  int64_t nnzb;         // kept blocks of the mask
   int first;            // logical id of the launch's first workgroup (set by the launcher)
   float scale;
   const int32_t *row_ptr, *col_idx, *col_ptr, *row_idx;
