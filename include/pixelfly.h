@@ -247,11 +247,12 @@ pf_status pf_layout_plan_get(const pf_layout *layout, int32_t *stats,
  * tokens at rank r runs on this layout (host only; the layout need not be
  * uploaded).  The rank-r products T_lr = X V^T and S = dY U report kernel 0
  * (r = 0, not run), 1 (the rank-r kernel, no split over workgroups)
- * or 2 (the tile kernel in dense mode), the number of workgroups that split
- * one output tile's K range (fp32 partials summed by a second pass when
- * above 1) and the output tile (tokens x columns).  The block-sparse
- * products report their output tile and kernel family (1: operands copied
- * global -> LDS directly; 0: staged through registers).  The weight
+ * or 2 (the tile kernel in dense mode) or 3 (fp32: the small-product
+ * kernel), the number of workgroups that split one output tile's K range
+ * (fp32 partials summed by a second pass when above 1) and the output tile
+ * (tokens x columns).  The block-sparse products report their output tile
+ * and kernel family (1: operands copied global -> LDS directly; 0: staged
+ * through registers; 2: the small-product kernel).  The weight
  * gradient reports its work items (kept-block tiles plus the dU and dV
  * tiles), the token split and the tokens per split, its tile side (128, or
  * 256 for the bf16 kernel whose 256 workgroups first run whole items and

@@ -192,9 +192,28 @@ int nt_band(bool dense, bool b_kn, int ntiles) {
   return !dense && !b_kn && ntiles >= 64 ? (ntiles + 7) / 8 : 0;
 }
 
+// Products of few 32 x 32 output tiles (workgroups) run on the small-product
+// kernel, whose waves split each tile's K list: up to two per CU for blocks
+// of 32, three for larger ones (whose tiles carry longer K lists), four for
+// fp32.  Large tiles against it, us: 1024 x 4096 b = 64 backward-data 18.7 /
+// 6.5 at 8 tokens (32 workgroups), 20.6 / 9.9 at 512 (512); 768 x 3072 b = 32
+// forward 7.8 / 5.1 at 8 tokens, 8.6 / 6.5 at 128 (384), 8.0 / 8.2 at 256
+// (768); 4096 square b = 128 forward 13.6 / 7.4 at 128 tokens (512), 14.3 /
+// 22.1 at 512 (2048); fp32 2048 square b = 64 forward 22.7 / 6.5 at 64 tokens
+// (128), 24.8 / 18.0 at 512 (1024), 26.2 / 32.8 at 1024 (2048).
+bool use_small(int dtype, int blk, int64_t M, int64_t slices) {
+  const int64_t lim = blk == 32 ? 512 : dtype == 0 ? 768 : 1024;
+  return (M + 31) / 32 * slices <= lim;
+}
+bool use_small_nt(int dtype, int blk, int G, int64_t M, int ntiles) {
+  return use_small(dtype, blk, M, (int64_t)ntiles * G * (blk / 32));
+}
+
 hipError_t nt_launch(pf_kernel_class kc, int dtype, int blk, int G, bool b_kn, int bm, int kmax,
                      const pf::NTArgs &a_in, hipStream_t s) {
   Timed t(kc, s);
+  if (!a_in.dense && use_small_nt(dtype, blk, G, a_in.M, a_in.ntiles))
+    return pf::launch_small(dtype, blk, G, b_kn, kmax, a_in, s);
   pf::NTArgs a = a_in;
   a.band = nt_band(a.dense != 0, b_kn, a.ntiles);
   const NTChoice c = nt_choose(dtype, blk, G, bm, kmax, a.M, a.ntiles, a.nsplit, a.dense != 0);
@@ -212,7 +231,8 @@ hipError_t nt_launch(pf_kernel_class kc, int dtype, int blk, int G, bool b_kn, i
 // A . B (B [k][n]), with M-tile bm; split over K when ws gives room.
 pf_status dense_nt(pf_kernel_class kc, int dtype, int blk, int G, bool b_kn, int bm, int64_t M,
                    const void *A, int64_t lda, const void *B, int64_t ldb, int nsteps, int nblk,
-                   void *C, int64_t ldc, int nsplit, float *ws, hipStream_t s, const char *what) {
+                   void *C, int64_t ldc, int nsplit, float *ws, hipStream_t s, const char *what,
+                   bool small = false) {
   pf::NTArgs a{};
   a.A = A; a.lda = lda; a.B = B; a.ldb = ldb;
   a.dense = 1; a.dense_nsteps = nsteps; a.dense_nblk = nblk;
@@ -221,6 +241,10 @@ pf_status dense_nt(pf_kernel_class kc, int dtype, int blk, int G, bool b_kn, int
   a.nsplit = nsplit;
   a.partials = ws;
   a.ldp = (int64_t)nblk * blk;
+  if (small) {
+    Timed t(kc, s);
+    return hip_status(pf::launch_small(dtype, blk, 1, b_kn, nsteps, a, s), what);
+  }
   const int per_split = (nsteps + std::max(1, nsplit) - 1) / std::max(1, nsplit);
   pf_status st = hip_status(nt_launch(kc, dtype, blk, G, b_kn, bm, per_split, a, s), what);
   if (st != PF_OK || nsplit <= 1) return st;
@@ -232,17 +256,19 @@ pf_status dense_nt(pf_kernel_class kc, int dtype, int blk, int G, bool b_kn, int
 // kernel (128 x 128 or 256 x 256 tiles, a K split with fp32 partials and a
 // reduction pass).  The rank-r kernel runs a product while 128 x 128 tiles
 // would cover fewer than PF_SKINNY_MAX_TILES of them (a quarter of the CUs)
-// and its busiest compute unit reads at most kSkinnyBytes, about 28 us of
-// operand bytes (skinny_tile): with few token rows every workgroup reads
-// the whole second operand, and for deep products the split, whose tiles
-// share it, wins despite its two passes (2509 x 16384 to r = 256: 4.2 MB, 49
-// us against 35 + 5; 2509 x 4096: 1 MB, 13.9 us against 15.3 + 5).
+// and its busiest compute unit reads at most kSkinnyBytes, about 15 us of
+// operand bytes (skinny_tile): with few token rows every workgroup reads its
+// part of the second operand whole, and for deep products the split wins
+// despite its two passes (rank-r kernel / split + reduction, us: 2509 x 4096
+// to r = 256, 1.0 MB, 14.8 / 14.6 + 5; 1500 x 8192 to r = 128, 1.6 MB, 17.6 /
+// 12.3 + 4.5; 128 x 16384 to r = 256, 2.1 MB, 30.9 / 10.1 + 4.6; 2509 x
+// 16384, 4.2 MB, 49 / 35 + 5).
 // S = dY U keeps the rank-r kernel one tile further for K up to 2048 (8192 x
 // 1024 to r = 128: 8.1 us against 9.9 + 5.4).
 #ifndef PF_SKINNY_MAX_TILES
 #define PF_SKINNY_MAX_TILES 64
 #endif
-constexpr int64_t kSkinnyBytes = 5 << 19;
+constexpr int64_t kSkinnyBytes = 5 << 18;
 // It addresses its operands through 32-bit buffer ranges and points what
 // lies past the end at the offset 0x7ffffff0, which must lie outside every
 // range: A's tile (64 K-long rows) and the whole r x K (or K x r) second
@@ -295,9 +321,14 @@ struct SkinnyPlan {
   int G;  // output blocks per tile (128 or 256 columns)
   int blk = 0;  // block width of the product's K-steps and output blocks
   bool skinny = false;  // the rank-r kernel (set by rank_plan_ws)
+  bool small = false;   // fp32: the small-product kernel
 };
 SkinnyPlan skinny_plan(int dtype, int blk, int64_t T, int kblocks, int r, bool s_side) {
   SkinnyPlan p{dtype == 0 ? 128 : 64, 1, 0, 128 / blk};
+  if (dtype != 0 && r > 0 && use_small(dtype, 32, T, r / 32)) {
+    p.small = true;
+    return p;
+  }
   if (dtype != 0 && r > 0 && r < 128) {
     // fp32, r below one 128-column tile: one block per tile (no dead columns).
     p.G = 1;
@@ -1004,10 +1035,10 @@ pf_status pf_linear_plan_get(const pf_layout *L, pf_dtype dtype, int64_t T, int3
     const int ksteps = (int)(K / rb);
     const NTChoice c = nt_choose(dt, rb, G, sp.bm, (ksteps + sp.nsplit - 1) / sp.nsplit, T,
                                  (r / rb + G - 1) / G, sp.nsplit, true);
-    v[0] = 2;
+    v[0] = sp.small ? 3 : 2;
     v[1] = sp.nsplit;
-    v[2] = c.bm;
-    v[3] = c.bn;
+    v[2] = sp.small ? 32 : c.bm;
+    v[3] = sp.small ? 32 : c.bn;
   };
   int32_t t[4] = {0, 0, 0, 0}, sv[4] = {0, 0, 0, 0};
   rank(L->n_in, L->nb_in, false, t);
@@ -1026,12 +1057,14 @@ pf_status pf_linear_plan_get(const pf_layout *L, pf_dtype dtype, int64_t T, int3
       use_bwd_pairs(L, dt, T, r)
           ? nt_choose(dt, 64, 1, 128, L->kmax_bwd_p + r / 64, T, (int)L->bwd_tiles_p.size(), 1, false)
           : nt_choose(dt, b, g.G, 128, g.kmax + r / b, T, g.ntiles, 1, false);
-  p.fwd_tile_m = cf.bm;
-  p.fwd_tile_n = cf.bn;
-  p.fwd_direct_lds = cf.dma;
-  p.bwd_tile_m = cg.bm;
-  p.bwd_tile_n = cg.bn;
-  p.bwd_direct_lds = cg.dma;
+  const bool fs = use_small_nt(dt, b, f.G, T, f.ntiles);
+  const bool gs = !use_bwd_pairs(L, dt, T, r) && use_small_nt(dt, b, g.G, T, g.ntiles);
+  p.fwd_tile_m = fs ? 32 : cf.bm;
+  p.fwd_tile_n = fs ? 32 : cf.bn;
+  p.fwd_direct_lds = fs ? 2 : cf.dma;
+  p.bwd_tile_m = gs ? 32 : cg.bm;
+  p.bwd_tile_n = gs ? 32 : cg.bn;
+  p.bwd_direct_lds = gs ? 2 : cg.dma;
   TNPlan tp;
   const pf::TNArgs a =
       tn_args(L, dtype, T, r, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, &tp);
@@ -1116,7 +1149,7 @@ pf_status linear_fwd(const pf_layout *L, pf_dtype dtype, int64_t T, int32_t r, c
     const int rb = sp.blk;
     st = dense_nt(PF_KERNEL_LOWRANK_T, dt, rb, sp.G, false, sp.bm, T, X, L->n_in, V, L->n_in,
                   (int)(L->n_in / rb), r / rb, T_lr, r, sp.nsplit, (float *)workspace, s,
-                  "T_lr kernel");
+                  "T_lr kernel", sp.small);
     if (st != PF_OK) return st;
   }
   pf::NTArgs a{};
@@ -1208,7 +1241,7 @@ pf_status enqueue_s(const pf_layout *L, int dt, int64_t T, int32_t r, const void
                        "S kernel");
   const int rb = sp.blk;
   return dense_nt(PF_KERNEL_LOWRANK_S, dt, rb, sp.G, true, sp.bm, T, dY, L->n_out, U, r,
-                  (int)(L->n_out / rb), r / rb, S, r, sp.nsplit, ws, s, "S kernel");
+                  (int)(L->n_out / rb), r / rb, S, r, sp.nsplit, ws, s, "S kernel", sp.small);
 }
 
 // dX = dY (M o W) + S V (optionally times gelu'(aux)).  pair_ws: room for

@@ -160,6 +160,16 @@ struct AttnArgs {
 // M-tile (tokens per workgroup): 128, or 64 for the skinny rank-r products.
 hipError_t launch_nt(int dtype, int blk, int G, bool b_kn, int bm, const NTArgs &a,
                      hipStream_t s);
+// NT products of few output tiles, bf16 and fp32 (small.hip): 32 x 32 output
+// tiles, the waves of a workgroup splitting the K list.  kmax: the most
+// K-blocks of any tile.  Dense mode: fp32 only.
+struct SmallArgs {
+  NTArgs nt;
+  int G;         // output blocks per tile of nt.tiles
+  int log2_blk;
+};
+hipError_t launch_small(int dtype, int blk, int G, bool b_kn, int kmax, const NTArgs &nt,
+                        hipStream_t s);
 // b = 32 backward-data pairs: Wp[p] (64 x 64 bf16) from the blocks of W that
 // src[4p .. 4p + 3] name (-1: zeros).
 hipError_t launch_pair_gather(const void *W, const int32_t *src, int npair, void *Wp,

@@ -40,6 +40,7 @@ hipError_t launch_pair_scatter(const void *, const int32_t *, int, void *, hipSt
   no_kernels("pair_scatter");
 }
 hipError_t launch_tn_reduce(int, int, const TNArgs &, hipStream_t) { no_kernels("tn_reduce"); }
+hipError_t launch_small(int, int, int, bool, int, const NTArgs &, hipStream_t) { no_kernels("small"); }
 hipError_t launch_skinny(bool, const SkinnyArgs &, hipStream_t) { no_kernels("skinny"); }
 hipError_t launch_mix_dgamma(int, const void *, const void *, int64_t, const float *, int,
                              float *, float *, hipStream_t) {

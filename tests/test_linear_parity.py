@@ -472,3 +472,60 @@ def test_deep_rank_product_without_workspace():
                               ws_bytes=n)
         torch.cuda.synchronize()
         check_close("S", to_host(S), ref, "bf16")
+
+
+@pytest.mark.parametrize("n_out,n_in,b,ms,T,r,dtype,gamma,epi", [
+    # one token; an odd number of K blocks of 32 (half a step dead), GELU
+    (96, 160, 32, 4, 1, 32, "bf16", None, 1),
+    # kept / low-rank switch inside a 128-byte step (bf16, blocks of 32), mixed
+    (768, 256, 32, 8, 33, 96, "bf16", 0.7, 1),
+    (512, 384, 64, 4, 70, 64, "bf16", 0.3, 0),
+    # column slices of 128-blocks, tiles of several block rows with a short last one
+    (1152, 256, 128, 2, 65, 128, "bf16", None, 1),
+    # no low-rank blocks; gamma = 1 drops them
+    (256, 512, 64, 8, 31, 0, "bf16", None, 0),
+    (256, 512, 64, 8, 31, 64, "bf16", 1.0, 0),
+    # fp32: eight waves (long K lists) and four, rank products on it too
+    (1024, 2048, 64, 32, 97, 192, "fp32", None, 1),
+    (96, 160, 32, 2, 3, 32, "fp32", 0.6, 1),
+    (384, 256, 128, 2, 130, 128, "fp32", None, 1),
+])
+def test_small_products(n_out, n_in, b, ms, T, r, dtype, gamma, epi):
+    """Forward and backward-data on the small-product kernel (32 x 32 output
+    tiles, K list split over the waves): ragged tokens, dead steps, the
+    switch to the low-rank blocks, every epilogue."""
+    torch = torch_cuda()
+    from paper_2112_00029_amd import pixelfly as pf
+    std = (1.0, 1.0 / np.sqrt(6 * 32), 1.0 / 32, 1.0) if dtype == "fp32" else (0.02,) * 4
+    inp = _inputs(n_out, n_in, b, ms, T, r, dtype, std=std)
+    L = pf.pf_layout_create(n_out, n_in, b, ms)
+    pf.pf_layout_upload(L)
+    plan = pf.pf_linear_plan_get(L, dtype, T, r)
+    print(f"[small] {n_out}x{n_in} b={b} T={T} r={r} {dtype} gamma={gamma} epi={epi}", flush=True)
+    assert (plan["fwd_direct_lds"], plan["bwd_direct_lds"]) == (2, 2), plan
+    assert r == 0 or plan["lowrank_t_kernel"] == plan["lowrank_s_kernel"] == (3 if dtype == "fp32" else 1)
+    d = {k: to_dev(v) for k, v in inp["raw"].items()}
+    H, Hr = synth.draw((T, n_in), 1.0, 0, 40, dtype)
+    aux = to_dev(Hr) if epi else None
+    Y, dX = empty((T, n_out), dtype), empty((T, n_in), dtype)
+    pre = empty((T, n_out), dtype) if epi else None
+    Tl, S = (empty((T, r), dtype) for _ in range(2)) if r else (None, None)
+    e = pf.PF_EPI_GELU if epi else pf.PF_EPI_NONE
+    lead = (L, dtype, T, r) if gamma is None else (L, dtype, T, r, gamma)
+    fwd = pf.pf_linear_fwd if gamma is None else pf.pf_linear_fwd_mixed
+    bwd = pf.pf_linear_bwd_data if gamma is None else pf.pf_linear_bwd_data_mixed
+    fwd(*lead, d["X"], d["W"], d["U"] if r else None, d["V"] if r else None, Y, Tl, e, pre)
+    bwd(*lead, d["dY"], d["W"], d["U"] if r else None, d["V"] if r else None, S, dX, e, aux)
+    torch.cuda.synchronize()
+    a, be = (1.0, 1.0) if gamma is None else (gamma, 1.0 - gamma)
+    Wd, U, V = inp["Wd"], inp["U"], inp["V"]
+    ref = a * (inp["X"] @ Wd.T) + (be * (inp["X"] @ V.T) @ U.T if r else 0.0)
+    gref = a * (inp["dY"] @ Wd) + (be * (inp["dY"] @ U) @ V if r else 0.0)
+    if epi:
+        check_close("Y_pre", to_host(pre), ref, dtype)
+        ref, gref = ol.gelu(ref), gref * ol.gelu_grad(H)
+    check_close("Y", to_host(Y), ref, dtype)
+    check_close("dX", to_host(dX), gref, dtype)
+    if r:
+        check_close("T_lr", to_host(Tl), inp["X"] @ V.T, dtype)
+        check_close("S", to_host(S), inp["dY"] @ U, dtype)
