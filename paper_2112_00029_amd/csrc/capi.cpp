@@ -269,6 +269,9 @@ pf_status dense_nt(pf_kernel_class kc, int dtype, int blk, int G, bool b_kn, int
 #define PF_SKINNY_MAX_TILES 64
 #endif
 constexpr int64_t kSkinnyBytes = 5 << 18;
+// Products deeper than this (the split was measured to 16384) keep the rank-r
+// kernel.
+constexpr int64_t kSplitMaxK = 65536;
 // It addresses its operands through 32-bit buffer ranges and points what
 // lies past the end at the offset 0x7ffffff0, which must lie outside every
 // range: A's tile (64 K-long rows) and the whole r x K (or K x r) second
@@ -284,7 +287,7 @@ bool skinny_small(int dtype, int64_t T, int r, int64_t K, bool s_side) {
 }
 bool use_skinny(int dtype, int64_t T, int r, int64_t K, bool s_side) {
   return skinny_small(dtype, T, r, K, s_side) &&
-         pf::skinny_tile(s_side, T, r).cost * 2 * K <= kSkinnyBytes;
+         (K > kSplitMaxK || pf::skinny_tile(s_side, T, r).cost * 2 * K <= kSkinnyBytes);
 }
 
 // bf16 rank-r product C[M x r] = A[M x K] . op(B) on the rank-r kernel
