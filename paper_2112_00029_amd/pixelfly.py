@@ -42,9 +42,9 @@ class PixelflyError(RuntimeError):
 # HIP/HSA runtime into the process, so torch tensors and streams are valid
 # for the library.
 try:
-    import torch  # noqa: F401
+    import torch
 except ImportError:
-    pass
+    torch = None
 
 if not os.path.exists(LIB_PATH):
     raise ImportError(
@@ -129,24 +129,27 @@ def header_functions() -> list[str]:
 
 
 def _ptr(x):
-    if x is None:
-        return None
-    if isinstance(x, int):
+    if x is None or isinstance(x, int):
         return x
     if hasattr(x, "data_ptr"):
         return x.data_ptr()
     raise TypeError(f"expected a tensor, int address or None, got {type(x)}")
 
 
+# The current stream's handle without building a torch.cuda.Stream object (a
+# call of the smallest products waits for the host: 3.7 -> 0.4 us of 9.1 / 5.7 us
+# for an attention forward of one block).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) if torch else None
+
+
 def _stream(s):
     if s is None:
-        try:
-            import torch
-            if torch.cuda.is_available() and torch.cuda.is_initialized():
-                return torch.cuda.current_stream().cuda_stream
-        except ImportError:
-            pass
-        return None
+        # An initialised runtime implies an available one.
+        if torch is None or not torch.cuda.is_initialized():
+            return None
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
+        return torch.cuda.current_stream().cuda_stream
     if isinstance(s, int):
         return s
     return s.cuda_stream
@@ -157,9 +160,14 @@ def _check(st: int):
         raise PixelflyError(st, _lib.pf_last_error().decode())
 
 
+_DTYPES = {"bf16": PF_BF16, "fp32": PF_FP32}
+
+
 def _dt(dtype) -> int:
     if isinstance(dtype, int):
         return dtype  # validated by the library
+    if isinstance(dtype, str) and dtype in _DTYPES:
+        return _DTYPES[dtype]
     name = str(dtype)
     if "bfloat16" in name or name == "bf16":
         return PF_BF16
