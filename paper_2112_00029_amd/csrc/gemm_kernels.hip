@@ -930,9 +930,17 @@ __global__ __launch_bounds__(256) void tn_reduce_kernel(TNArgs a_arg) {
   TNItemView<T, BLK> v;
   v.decode(a, item);
   const int q = (part * 256 + threadIdx.x) * 4;  // partial index
-  const int lane = q % 64, j = (q / 64) % 16, tn = (q / 1024) % 2, tm = (q / 2048) % 2, wave = q / 4096;
-  const int rl = (wave >> 1) * 64 + tm * 32 + (j >> 2) * 8 + (lane >> 5) * 4 + (j & 3);
-  const int cl = (wave & 1) * 64 + tn * 32 + (lane & 31);
+  const int tn = (q / 1024) % 2, tm = (q / 2048) % 2, wave = q / 4096;
+  int rl = (wave >> 1) * 64 + tm * 32, cl = (wave & 1) * 64 + tn * 32;
+  if constexpr (std::is_same<T, bf16_t>::value) {  // [wave][tm][tn][q][lane][4] (gemm_tnd.hip)
+    const int lane = (q / 4) % 64;
+    rl += lane & 31;
+    cl += (q / 256) % 4 * 8 + (lane >> 5) * 4;
+  } else {
+    const int lane = q % 64, j = (q / 64) % 16;
+    rl += (j >> 2) * 8 + (lane >> 5) * 4 + (j & 3);
+    cl += lane & 31;
+  }
   const int ga = rl / BLK, gb = cl / BLK;
   const int blk = v.oblk(ga, gb);
   float wd = 0.f;
@@ -1140,7 +1148,6 @@ hipError_t launch_tn_reduce_t(int blk, const TNArgs &a, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 #if PF_GK_HAS(5)
-template hipError_t launch_tn_t<bf16_t>(int, const TNArgs &, hipStream_t);
 template hipError_t launch_tn_reduce_t<bf16_t>(int, const TNArgs &, hipStream_t);
 #endif
 #if PF_GK_HAS(6)
@@ -1172,7 +1179,7 @@ hipError_t launch_reduce_rows(int dtype, int nsplit, const float *P, int64_t M, 
 }
 
 hipError_t launch_tn(int dtype, int blk, const TNArgs &a, hipStream_t s) {
-  return dtype == 0 ? launch_tn_t<bf16_t>(blk, a, s) : launch_tn_t<float>(blk, a, s);
+  return dtype == 0 ? launch_tnd(blk, a, s) : launch_tn_t<float>(blk, a, s);
 }
 
 hipError_t launch_tn_reduce(int dtype, int blk, const TNArgs &a, hipStream_t s) {

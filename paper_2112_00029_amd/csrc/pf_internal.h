@@ -209,6 +209,8 @@ hipError_t launch_reduce_rows(int dtype, int nsplit, const float *P, int64_t M, 
 // The TN kernel, and (a.nsplit > 1) the pass that sums its split partials.
 hipError_t launch_tn(int dtype, int blk, const TNArgs &a, hipStream_t s);
 hipError_t launch_tn_reduce(int dtype, int blk, const TNArgs &a, hipStream_t s);
+// The bf16 128 x 128 weight gradient (gemm_tnd.hip).
+hipError_t launch_tnd(int blk, const TNArgs &a, hipStream_t s);
 // bf16 weight gradient on 256 x 256 tiles (blk 64 or 128) on kTNWGrid
 // workgroups, or one per item when fewer (gemm_tnw.hip), and the pass that
 // sums its `shared` items.
@@ -229,7 +231,6 @@ extern template hipError_t launch_nt_tb<uint16_t, false>(int, int, int, bool, co
 extern template hipError_t launch_nt_tb<uint16_t, true>(int, int, int, bool, const NTArgs &, hipStream_t);
 extern template hipError_t launch_nt_tb<float, false>(int, int, int, bool, const NTArgs &, hipStream_t);
 extern template hipError_t launch_nt_tb<float, true>(int, int, int, bool, const NTArgs &, hipStream_t);
-extern template hipError_t launch_tn_t<uint16_t>(int, const TNArgs &, hipStream_t);
 extern template hipError_t launch_tn_t<float>(int, const TNArgs &, hipStream_t);
 extern template hipError_t launch_tn_reduce_t<uint16_t>(int, const TNArgs &, hipStream_t);
 extern template hipError_t launch_tn_reduce_t<float>(int, const TNArgs &, hipStream_t);
