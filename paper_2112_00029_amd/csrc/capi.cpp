@@ -458,11 +458,16 @@ TNPlan tn_plan(int items, int64_t T, int64_t row_bytes, int64_t min_tokens = 512
   if (items < PF_TN_ROUND_ITEMS) {
     // Few items: the split that finishes soonest when kTNSlots workgroups
     // run at a time, i.e. fewest (rounds x 64-token steps per workgroup);
-    // the smaller split on ties (fewer partials).
+    // the smaller split on ties (fewer partials).  In bf16, where a step takes
+    // about 1.5 us, a split's partials (64 KiB an item, written and read back
+    // at 4.5 TB/s) count as items / 52 steps (4096 -> 1024 b = 64 at 8192
+    // tokens, 136 items: seven splits 49.5 + 11.0 us, three
+    // 45.3 + 6.6).
     int64_t best = -1;
     for (int64_t c = 1; c <= cap; ++c) {
       const int64_t chunk = ((T + c - 1) / c + 63) / 64 * 64, nsr = (T + chunk - 1) / chunk;
-      const int64_t cost = ((items * nsr + kTNSlots - 1) / kTNSlots) * (chunk / 64);
+      int64_t cost = ((items * nsr + kTNSlots - 1) / kTNSlots) * (chunk / 64) * 52;
+      if (min_tokens == 512 && nsr > 1) cost += nsr * items;
       if (best < 0 || cost < best) {
         best = cost;
         ns = nsr;
