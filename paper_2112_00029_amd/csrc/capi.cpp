@@ -1511,10 +1511,18 @@ pf_status pf_linear_bwd_weight_mixed(const pf_layout *L, pf_dtype dtype, int64_t
   float *wparts = (float *)((char *)workspace + off);
   float *sparts = wparts + (size_t)items * 16;
   a.wdot_out = wparts;
+  const bool dot_in_reduce = a.nsplit > 1 && r > 0;
+  if (dot_in_reduce) {
+    a.dot_s = S;
+    a.dot_t = T_lr;
+    a.dot_n = T * r;
+    a.dot_out = sparts;
+  }
   hipStream_t s = (hipStream_t)stream;
   if ((st = enqueue_tn(L, (int)dtype, a, p, (float *)workspace, s)) != PF_OK) return st;
   Timed t(PF_KERNEL_REDUCE, s);
-  return hip_status(pf::launch_mix_dgamma((int)dtype, S, T_lr, r > 0 ? T * r : 0, wparts,
+  return hip_status(pf::launch_mix_dgamma((int)dtype, dot_in_reduce ? nullptr : S, T_lr,
+                                          r > 0 ? T * r : 0, wparts,
                                           a.nsplit > 1 ? items * 16 : items, sparts, dgamma, s),
                     "dgamma kernels");
 }

@@ -918,6 +918,18 @@ __global__ __launch_bounds__(256, 2) void tn_kernel(TNArgs a_arg) {
   }
 }
 
+// Partial b of <S, T_lr> (n elements, kMixDotParts workgroups of 256).
+template <typename T>
+__device__ __forceinline__ void mix_dot_part(const T *__restrict__ S, const T *__restrict__ Tl,
+                                             int64_t n, int b, float *__restrict__ out) {
+  float x = 0.f;
+  for (int64_t i = (int64_t)b * 256 + threadIdx.x; i < n; i += (int64_t)kMixDotParts * 256)
+    x += to_f<T>(S[i]) * to_f<T>(Tl[i]);
+  __shared__ float red[4];
+  const float tot = block_sum256(x, red);
+  if (threadIdx.x == 0) out[b] = tot;
+}
+
 // Second pass of a split TN product: sum the split partials in split order
 // and store the kept blocks.  Workgroup (item, part): 16 parts of 1024
 // partial sums per item; each thread takes 4 consecutive partial sums
@@ -927,6 +939,11 @@ __global__ __launch_bounds__(256) void tn_reduce_kernel(TNArgs a_arg) {
   const TNArgs a = a_arg;
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
   const int item = bid / 16, part = bid % 16;
+  if (a.dot_out && item >= tn_items_total_dev(a, 128 / BLK)) {
+    mix_dot_part<T>((const T *)a.dot_s, (const T *)a.dot_t, a.dot_n,
+                    bid - tn_items_total_dev(a, 128 / BLK) * 16, a.dot_out);
+    return;
+  }
   TNItemView<T, BLK> v;
   v.decode(a, item);
   const int q = (part * 256 + threadIdx.x) * 4;  // partial index
@@ -990,12 +1007,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void mix_dot_kernel(const T *__restrict__ S,
                                                       const T *__restrict__ Tl, int64_t n,
                                                       float *__restrict__ out) {
-  float x = 0.f;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)kMixDotParts * 256)
-    x += to_f<T>(S[i]) * to_f<T>(Tl[i]);
-  __shared__ float red[4];
-  const float tot = block_sum256(x, red);
-  if (threadIdx.x == 0) out[blockIdx.x] = tot;
+  mix_dot_part<T>(S, Tl, n, blockIdx.x, out);
 }
 
 #if PF_GK_HAS(0)
@@ -1013,7 +1025,7 @@ __global__ __launch_bounds__(256) void mix_final_kernel(const float *__restrict_
 hipError_t launch_mix_dgamma(int dtype, const void *S, const void *T_lr, int64_t n,
                              const float *wparts, int nw, float *sparts, float *dgamma,
                              hipStream_t s) {
-  if (n > 0) {
+  if (n > 0 && S) {
     if (dtype == 0)
       launch_kernel(mix_dot_kernel<bf16_t>, dim3(kMixDotParts), dim3(256), s, (const bf16_t *)S,
                     (const bf16_t *)T_lr, n, sparts);
@@ -1124,8 +1136,9 @@ static hipError_t tn_go(const TNArgs &a, hipStream_t s) {
 template <typename T, int BLK>
 static hipError_t tn_reduce_go(const TNArgs &a, hipStream_t s) {
   const int64_t items = tn_items_total(a, BLK);
-  if (items <= 0 || items * 16 > 0x7fffffff) return hipErrorInvalidValue;
-  launch_kernel(tn_reduce_kernel<T, BLK>, dim3((unsigned)(items * 16)), dim3(256), s, a);
+  if (items <= 0 || items * 16 > 0x7fffffff - kMixDotParts) return hipErrorInvalidValue;
+  const int64_t grid = items * 16 + (a.dot_out ? kMixDotParts : 0);
+  launch_kernel(tn_reduce_kernel<T, BLK>, dim3((unsigned)grid), dim3(256), s, a);
   return hipGetLastError();
 }
 

@@ -123,6 +123,11 @@ struct TNArgs {
   float scale_w, scale_lr;
   const void *wdot;
   float *wdot_out;
+  // With dot_out set, kMixDotParts further workgroups of the split reduction
+  // form the partials of <dot_s, dot_t> (dot_n elements: S and T_lr) there.
+  const void *dot_s, *dot_t;
+  int64_t dot_n;
+  float *dot_out;
   // Launch order: launch position i (within a split) runs item order[i]
   // when n_order > 0, item i otherwise.
   int n_order;
@@ -263,7 +268,9 @@ inline SkinnyTile skinny_tile(bool b_kn, int64_t M, int ncols) {
 // dgamma of the mixing weight: partial sums of <S, T_lr> (n elements,
 // kMixDotParts workgroups), then one workgroup adds the kernel-stored partial
 // dot products wparts[0 .. nw) and subtracts the S.T_lr partials, in a fixed
-// order, into *dgamma.
+// order, into *dgamma.  With S null (and n > 0) the S.T_lr partials are in
+// sparts already: the split reduction formed them in its own launch (TNArgs
+// dot_out; a launch of its own took 4.8 us of the 2100-token mixed step).
 constexpr int kMixDotParts = 256;
 hipError_t launch_mix_dgamma(int dtype, const void *S, const void *T_lr, int64_t n,
                              const float *wparts, int nw, float *sparts, float *dgamma,
