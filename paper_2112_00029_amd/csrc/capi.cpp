@@ -183,6 +183,12 @@ NTChoice nt_choose(int dtype, int blk, int G, int bm, int kmax, int64_t M, int n
     if (!dense && steps <= 8 && wg <= 768) return NTChoice{true, pf::NTD_SHORT_K, 128, 128};
     return NTChoice{true, pf::NTD_DEFAULT, 128, 128};
   }
+  // 256 x 64 tiles that would give no CU a second one: half the token rows
+  // (1024 x 4096 b = 64 backward-data at 1024, 2100, 4096 tokens, 64 - 256
+  // tiles: 20.9 -> 17.4, 21.2 -> 20.1, 22.9 -> 22.0 us; at 272 tiles, 4100 x
+  // 2048 x 1024, 15.1 -> 16.4, at 512 30.6 -> 42.6).
+  if (w == 64 && !dense && (M + 255) / 256 * ntiles <= 256)
+    return NTChoice{true, pf::NTD_SHORT_K, 128, w};
   return NTChoice{true, pf::NTD_DEFAULT, 256, w};  // 256 x 256 and 256 x 64 tiles
 }
 

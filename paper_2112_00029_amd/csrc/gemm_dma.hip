@@ -548,7 +548,8 @@ hipError_t ntd_go(const NTArgs &a, hipStream_t s) {
 //        lists) 128 x 128 tiles with K-steps of 32 in three stages, three
 //        workgroups per CU;
 //   256: 256 x 256 tiles, 8 waves of 128 x 64, one workgroup per CU;
-//    64: 256 x  64 tiles, 4 waves, two workgroups per CU.
+//    64: 256 x  64 tiles, 4 waves, two workgroups per CU; or (few tiles) 128
+//        x 64 tiles in three stages.
 // The others take K-steps of 64 in two stages.  The 8-wave tiles read half
 // the operand bytes per flop of the 128 x 128 ones and keep two waves per
 // SIMD; the short-K variant keeps more workgroups per CU in flight when each
@@ -563,6 +564,8 @@ hipError_t ntd_cfg(int variant, const NTArgs &a, hipStream_t s) {
   } else if constexpr (BN == 256) {
     return ntd_go<BLK, G, BKN, 256, 64, 2, 8, DENSE, 1>(a, s);
   } else if constexpr (BN == 64) {
+    if constexpr (!DENSE)
+      if (variant == NTD_SHORT_K) return ntd_go<BLK, G, BKN, 128, 64, 3, 4, DENSE, 2>(a, s);
     return ntd_go<BLK, G, BKN, 256, 64, 2, 4, DENSE, 2>(a, s);
   }
   return hipErrorInvalidValue;
