@@ -11,7 +11,7 @@
 //             K-steps run over every block of a dense B; the K range may be
 //             split over workgroups that write fp32 partial outputs, summed
 //             in split order by reduce_rows_kernel (deterministic).
-//  tn_kernel  out = A^T . B reduced over tokens, only for kept blocks
+//  tn_kernel  (fp32) out = A^T . B reduced over tokens, only for kept blocks
 //             (weight gradient restricted to the mask) plus dense regions
 //             (dU = dY^T T_lr, dV = S^T X).  The token range may be split
 //             over workgroups; tn_reduce_kernel sums the partials in split
@@ -111,20 +111,6 @@ __device__ __forceinline__ bf16x8 frag_kmajor(const bf16_t *base, int ld,
   int n0 = (g16 & 1) * 16, kb = (g16 >> 1) * 8;
   const bf16_t *p = base + (ks * 16 + kb + (i >> 2)) * ld + row0 + n0 + (i & 3) * 4;
   return cat8(tr16(p), tr16(p + 4 * ld));
-}
-
-// Same fragment from an unpadded [k][128] tile (256-byte k rows) whose
-// 16-byte chunks are XOR-swizzled by k: chunk c of k row k sits at chunk
-// c ^ ((k & 3) << 2).  The four k rows one 16-lane group reads then fall in
-// four different 64-byte bank groups (no LDS bank conflicts).
-__device__ __forceinline__ int swz128(int k, int col) {
-  return k * 128 + ((((col >> 3) ^ ((k & 3) << 2)) << 3) | (col & 7));
-}
-__device__ __forceinline__ bf16x8 frag_kmajor_swz(const bf16_t *base, int ks, int row0, int lane) {
-  const int g16 = lane >> 4, i = lane & 15;
-  const int k = ks * 16 + (g16 >> 1) * 8 + (i >> 2);
-  const int col = row0 + (g16 & 1) * 16 + (i & 3) * 4;
-  return cat8(tr16(base + swz128(k, col)), tr16(base + swz128(k + 4, col)));
 }
 
 // MFMA (32x32x16) fragment of a 32-row operand stored [row][k] in LDS.
@@ -713,26 +699,22 @@ __device__ __forceinline__ int tn_pidx(int wave, int tm, int tn, int j, int lane
   return (((wave * 2 + tm) * 2 + tn) * 16 + j) * 64 + lane;
 }
 
-template <typename T, int BLK>
+template <int BLK>
 __global__ __launch_bounds__(256, 2) void tn_kernel(TNArgs a_arg) {
   const TNArgs a = a_arg;  // local copy: lambdas below capture it by reference
-  constexpr bool BF = std::is_same<T, bf16_t>::value;
   constexpr int GT = 128 / BLK;  // blocks per tile side
-  constexpr int BKT = BF ? 64 : 32, TILE = 128;
-  constexpr int VEC = 16 / (int)sizeof(T);
-  constexpr int LDS_S = TILE + (BF ? 0 : 4);  // bf16: unpadded, chunk-swizzled rows
+  constexpr int BKT = 32, TILE = 128;
+  constexpr int VEC = 4;  // floats of a 16-byte chunk
+  constexpr int LDS_S = TILE + 4;
   constexpr int OP_ELEMS = BKT * LDS_S;
   constexpr int CPB = BKT * BLK / VEC;  // chunks of one block column slab
   constexpr int CH = GT * CPB, LD = CH / 256;
   constexpr int TM = 2, TN = 2;  // 4 waves as 2 x 2, 64 x 64 each
   static_assert(CPB % 256 == 0 && LD <= 8, "chunking");
 
-  // Two stages of both operands; the fp32 epilogue tile (128 x 132) reuses
-  // the same memory.
-  constexpr int SMEM_ELEMS = 2 * 2 * OP_ELEMS > TILE * (TILE + 4) * 4 / (int)sizeof(T)
-                                 ? 2 * 2 * OP_ELEMS
-                                 : TILE * (TILE + 4) * 4 / (int)sizeof(T);
-  __shared__ __attribute__((aligned(16))) T smem[SMEM_ELEMS];
+  // Two stages of both operands; the epilogue tile (128 x 132) reuses the
+  // same memory.
+  __shared__ __attribute__((aligned(16))) float smem[2 * 2 * OP_ELEMS];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -744,7 +726,7 @@ __global__ __launch_bounds__(256, 2) void tn_kernel(TNArgs a_arg) {
   // local copy keeps the scalar fields only.
   const int item = a.n_order > 0 ? (int)a_arg.order[pos] : pos;
 
-  TNItemView<T, BLK> v;
+  TNItemView<float, BLK> v;
   v.decode(a, item);
 
   bool live[TM][TN];
@@ -760,17 +742,17 @@ __global__ __launch_bounds__(256, 2) void tn_kernel(TNArgs a_arg) {
 
   // Token rows past t_end read as zeros (buffer range).  Column offsets of
   // each chunk are fixed for the whole loop.
-  const T *const a_base = v.Ab + t_begin * v.lda, *const b_base = v.Bb + t_begin * v.ldb;
-  const int64_t a_bytes = (t_end - t_begin) * v.lda * (int64_t)sizeof(T);
-  const int64_t b_bytes = (t_end - t_begin) * v.ldb * (int64_t)sizeof(T);
-  const uint32_t lda_b = (uint32_t)(v.lda * sizeof(T)), ldb_b = (uint32_t)(v.ldb * sizeof(T));
+  const float *const a_base = v.Ab + t_begin * v.lda, *const b_base = v.Bb + t_begin * v.ldb;
+  const int64_t a_bytes = (t_end - t_begin) * v.lda * (int64_t)sizeof(float);
+  const int64_t b_bytes = (t_end - t_begin) * v.ldb * (int64_t)sizeof(float);
+  const uint32_t lda_b = (uint32_t)(v.lda * sizeof(float)), ldb_b = (uint32_t)(v.ldb * sizeof(float));
   uint32_t offA[LD], offB[LD];
   static_for<LD>([&](auto i) __attribute__((always_inline)) {
     constexpr int g = (i * 256) / CPB;
     const int r = (tid + i * 256) % CPB;
     const uint32_t t = r / (BLK / VEC), cb = (r % (BLK / VEC)) * 16;
-    offA[i] = t * lda_b + (uint32_t)(v.acol(g) * BLK * sizeof(T)) + cb;
-    offB[i] = t * ldb_b + (uint32_t)(v.bcol(g) * BLK * sizeof(T)) + cb;
+    offA[i] = t * lda_b + (uint32_t)(v.acol(g) * BLK * sizeof(float)) + cb;
+    offB[i] = t * ldb_b + (uint32_t)(v.bcol(g) * BLK * sizeof(float)) + cb;
   });
   auto load = [&](int s, Stage8 &ra, Stage8 &rb) __attribute__((always_inline)) {
     const rsrc_t rA = make_rsrc(a_base, a_bytes), rB = make_rsrc(b_base, b_bytes);
@@ -781,13 +763,13 @@ __global__ __launch_bounds__(256, 2) void tn_kernel(TNArgs a_arg) {
     });
   };
   auto store = [&](Stage8 &ra, Stage8 &rb, int buf) __attribute__((always_inline)) {
-    T *As = smem + buf * 2 * OP_ELEMS;
-    T *Bs = As + OP_ELEMS;
+    float *As = smem + buf * 2 * OP_ELEMS;
+    float *Bs = As + OP_ELEMS;
     static_for<LD>([&](auto i) __attribute__((always_inline)) {
       constexpr int g = (i * 256) / CPB;
       const int r = (tid + i * 256) % CPB;
       const int t = r / (BLK / VEC), c = g * BLK + (r % (BLK / VEC)) * VEC;
-      const int o = BF ? swz128(t, c) : t * LDS_S + c;
+      const int o = t * LDS_S + c;
       *(u32x4 *)(As + o) = ra.template at<i>();
       *(u32x4 *)(Bs + o) = rb.template at<i>();
     });
@@ -802,53 +784,30 @@ __global__ __launch_bounds__(256, 2) void tn_kernel(TNArgs a_arg) {
   });
 
   auto compute = [&](int buf, int) __attribute__((always_inline)) {
-    const T *As = smem + buf * 2 * OP_ELEMS;
-    const T *Bs = As + OP_ELEMS;
-    if constexpr (BF) {
-      static_for<BKT / 16>([&](auto ks) __attribute__((always_inline)) {
-        bf16x8 af[TM], bfg[TN];
-        static_for<TM>([&](auto tm) __attribute__((always_inline)) {
-          af[tm] = frag_kmajor_swz((const bf16_t *)As, ks, wm * 64 + tm * 32, lane);
-        });
+    const float *As = smem + buf * 2 * OP_ELEMS;
+    const float *Bs = As + OP_ELEMS;
+    static_for<BKT / 2>([&](auto ks) __attribute__((always_inline)) {
+      float af[TM], bfg[TN];
+      const int kq = ks * 2 + (lane >> 5);
+      static_for<TM>([&](auto tm) __attribute__((always_inline)) {
+        af[tm] = As[kq * LDS_S + wm * 64 + tm * 32 + (lane & 31)];
+      });
+      static_for<TN>([&](auto tn) __attribute__((always_inline)) {
+        bfg[tn] = Bs[kq * LDS_S + wn * 64 + tn * 32 + (lane & 31)];
+      });
+      // fp32 MFMAs are long (the kernel is MFMA-bound at these sizes):
+      // sub-tiles without a kept block are skipped (a wave-uniform branch).
+      static_for<TM>([&](auto tm) __attribute__((always_inline)) {
         static_for<TN>([&](auto tn) __attribute__((always_inline)) {
-          bfg[tn] = frag_kmajor_swz((const bf16_t *)Bs, ks, wn * 64 + tn * 32, lane);
-        });
-        // All four sub-tiles, live or not: a branch per MFMA splits the step
-        // into blocks the scheduler cannot overlap (the next slice's LDS reads
-        // then wait behind every MFMA), and MFMA time is not what bounds this
-        // kernel.  A dead sub-tile reads clamped, valid fragments and is
-        // never stored.
-        static_for<TM>([&](auto tm) __attribute__((always_inline)) {
-          static_for<TN>([&](auto tn) __attribute__((always_inline)) {
-            acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[tm], bfg[tn], acc[tm][tn], 0, 0, 0);
-          });
+          if (live[tm][tn])
+            acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[tm], bfg[tn], acc[tm][tn], 0, 0, 0);
         });
       });
-    } else {
-      static_for<BKT / 2>([&](auto ks) __attribute__((always_inline)) {
-        float af[TM], bfg[TN];
-        const int kq = ks * 2 + (lane >> 5);
-        static_for<TM>([&](auto tm) __attribute__((always_inline)) {
-          af[tm] = As[kq * LDS_S + wm * 64 + tm * 32 + (lane & 31)];
-        });
-        static_for<TN>([&](auto tn) __attribute__((always_inline)) {
-          bfg[tn] = Bs[kq * LDS_S + wn * 64 + tn * 32 + (lane & 31)];
-        });
-        // fp32 MFMAs are long (the kernel is MFMA-bound at these sizes):
-        // sub-tiles without a kept block are skipped (a wave-uniform branch).
-        static_for<TM>([&](auto tm) __attribute__((always_inline)) {
-          static_for<TN>([&](auto tn) __attribute__((always_inline)) {
-            if (live[tm][tn])
-              acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[tm], bfg[tn], acc[tm][tn], 0, 0, 0);
-          });
-        });
-      });
-    }
+    });
   };
 
-  Stage8 ra0, rb0, ra1, rb1, ra2, rb2, ra3, rb3;
-  if constexpr (BF) pipeline4(nsteps, ra0, rb0, ra1, rb1, ra2, rb2, ra3, rb3, load, store, compute);
-  else pipeline2(nsteps, ra0, rb0, ra1, rb1, load, store, compute);
+  Stage8 ra0, rb0, ra1, rb1;
+  pipeline2(nsteps, ra0, rb0, ra1, rb1, load, store, compute);
 
   if (a.nsplit > 1) {
     float *part = a.partials + ((int64_t)item * a.nsplit + split) * (TILE * TILE);
@@ -862,11 +821,11 @@ __global__ __launch_bounds__(256, 2) void tn_kernel(TNArgs a_arg) {
     });
     return;
   }
-  // Stage the 128 x 128 tile in LDS (fp32), then write each kept b x b block
+  // Stage the 128 x 128 tile in LDS, then write each kept b x b block
   // with 16-byte stores of 8 consecutive columns.
   constexpr int CS = TILE + 4;
   static_assert(TILE * CS * 4 <= (int)sizeof(smem), "epilogue tile");
-  float *Cs = (float *)smem;
+  float *Cs = smem;
   __syncthreads();
   static_for<TM>([&](auto tm) __attribute__((always_inline)) {
     static_for<TN>([&](auto tn) __attribute__((always_inline)) {
@@ -889,25 +848,16 @@ __global__ __launch_bounds__(256, 2) void tn_kernel(TNArgs a_arg) {
         const float *src = Cs + (ga * BLK + rl) * CS + gb * BLK + c8;
         f32x4 lo = *(const f32x4 *)src, hi = *(const f32x4 *)(src + 4);
         if (a.wdot && v.sparse) {
-          const T *wp = (const T *)a.wdot + (int64_t)blk * (BLK * BLK) + rl * BLK + c8;
+          const float *wp = (const float *)a.wdot + (int64_t)blk * (BLK * BLK) + rl * BLK + c8;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) wd += lo[e] * to_f<T>(wp[e]) + hi[e] * to_f<T>(wp[4 + e]);
+          for (int e = 0; e < 4; ++e) wd += lo[e] * wp[e] + hi[e] * wp[4 + e];
         }
         lo *= sc;
         hi *= sc;
-        T *dst = v.sparse ? (T *)a.Wout + (int64_t)blk * (BLK * BLK) + rl * BLK + c8
-                          : v.dout + ((int64_t)v.acol(ga) * BLK + rl) * v.ldo + (int64_t)v.bcol(gb) * BLK + c8;
-        if constexpr (BF) {
-          u32x4 w;
-          w[0] = (uint32_t)f2bf(lo[0]) | ((uint32_t)f2bf(lo[1]) << 16);
-          w[1] = (uint32_t)f2bf(lo[2]) | ((uint32_t)f2bf(lo[3]) << 16);
-          w[2] = (uint32_t)f2bf(hi[0]) | ((uint32_t)f2bf(hi[1]) << 16);
-          w[3] = (uint32_t)f2bf(hi[2]) | ((uint32_t)f2bf(hi[3]) << 16);
-          *(u32x4 *)dst = w;
-        } else {
-          *(f32x4 *)dst = lo;
-          *(f32x4 *)(dst + 4) = hi;
-        }
+        float *dst = v.sparse ? (float *)a.Wout + (int64_t)blk * (BLK * BLK) + rl * BLK + c8
+                              : v.dout + ((int64_t)v.acol(ga) * BLK + rl) * v.ldo + (int64_t)v.bcol(gb) * BLK + c8;
+        *(f32x4 *)dst = lo;
+        *(f32x4 *)(dst + 4) = hi;
       }
     }
   });
@@ -1125,11 +1075,11 @@ template hipError_t launch_nt_tb<float, false>(int, int, int, bool, const NTArgs
 template hipError_t launch_nt_tb<float, true>(int, int, int, bool, const NTArgs &, hipStream_t);
 #endif
 
-template <typename T, int BLK>
+template <int BLK>
 static hipError_t tn_go(const TNArgs &a, hipStream_t s) {
   const int64_t grid = (int64_t)tn_items_total(a, BLK) * a.nsplit;
   if (grid <= 0 || grid > 0x7fffffff) return hipErrorInvalidValue;
-  launch_kernel(tn_kernel<T, BLK>, dim3((unsigned)grid), dim3(256), s, a);
+  launch_kernel(tn_kernel<BLK>, dim3((unsigned)grid), dim3(256), s, a);
   return hipGetLastError();
 }
 
@@ -1142,15 +1092,18 @@ static hipError_t tn_reduce_go(const TNArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_tn_t(int blk, const TNArgs &a, hipStream_t s) {
+#if PF_GK_HAS(6)
+hipError_t launch_tn_f32(int blk, const TNArgs &a, hipStream_t s) {
   switch (blk) {
-    case 32: return tn_go<T, 32>(a, s);
-    case 64: return tn_go<T, 64>(a, s);
-    case 128: return tn_go<T, 128>(a, s);
+    case 32: return tn_go<32>(a, s);
+    case 64: return tn_go<64>(a, s);
+    case 128: return tn_go<128>(a, s);
   }
   return hipErrorInvalidValue;
 }
+#else
+hipError_t launch_tn_f32(int blk, const TNArgs &a, hipStream_t s);
+#endif
 template <typename T>
 hipError_t launch_tn_reduce_t(int blk, const TNArgs &a, hipStream_t s) {
   switch (blk) {
@@ -1164,7 +1117,6 @@ hipError_t launch_tn_reduce_t(int blk, const TNArgs &a, hipStream_t s) {
 template hipError_t launch_tn_reduce_t<bf16_t>(int, const TNArgs &, hipStream_t);
 #endif
 #if PF_GK_HAS(6)
-template hipError_t launch_tn_t<float>(int, const TNArgs &, hipStream_t);
 template hipError_t launch_tn_reduce_t<float>(int, const TNArgs &, hipStream_t);
 #endif
 
@@ -1192,7 +1144,7 @@ hipError_t launch_reduce_rows(int dtype, int nsplit, const float *P, int64_t M, 
 }
 
 hipError_t launch_tn(int dtype, int blk, const TNArgs &a, hipStream_t s) {
-  return dtype == 0 ? launch_tnd(blk, a, s) : launch_tn_t<float>(blk, a, s);
+  return dtype == 0 ? launch_tnd(blk, a, s) : launch_tn_f32(blk, a, s);
 }
 
 hipError_t launch_tn_reduce(int dtype, int blk, const TNArgs &a, hipStream_t s) {
