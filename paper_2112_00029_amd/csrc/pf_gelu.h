@@ -6,30 +6,46 @@
 namespace pf {
 namespace {
 
-// Standard normal CDF: Phi(x) = 1 - tail for x >= 0 and tail for x < 0, with
-//   tail = erfc(|x| / sqrt 2) / 2 = t P(t) exp(-x^2 / 2), t = 1 / (1 + p |x| / sqrt 2),
-// P a degree-8 minimax fit (relative error 7e-9, iteratively reweighted
-// least squares over |x| / sqrt 2 in [0, 8], p = 0.371) of erfcx(z) / (2 t).
-// One reciprocal, one exponential and about fifteen other VALU instructions,
-// where the library erff takes some fifty on both sides of its branch: the
-// GELU epilogues of the 8192 x 1024 -> 4096 layer were bound by them (forward
-// 87 -> 72 us, backward-data 101 -> 80 us).  fp32 error of gelu over
-// |x| <= 3, 2-norm: 3.3e-8 (erff: 3.6e-8); the negative tail keeps its
-// relative accuracy (2e-7, where 1 + erf cancels).  e: exp(-x^2 / 2).
+// Standard normal CDF.  Near zero (|x| < 1.25) Phi(x) = 1/2 + x P(x^2), P of
+// degree 5 (a minimax fit of erf, 2e-9 absolute).  Beyond, the form of
+// Hastings (Abramowitz and Stegun 7.1.26): Phi(x) = 1 - tail for x > 0 and tail
+// for x < 0, with
+//   tail = erfc(|x| / sqrt 2) / 2 = t Q(t) exp(-x^2 / 2), t = 1 / (1 + p |x| / sqrt 2),
+// Q of degree 5 to erfcx(z) / (2 t), p = 0.45 (fitted here over |x| in [1.25,
+// 10]: within 5e-9 absolute and 4e-7 relative).
+// One reciprocal, one exponential and about twenty other VALU instructions
+// without a branch, where the library erff takes some fifty on both sides of
+// its own (both GELU launches of the 8192-token 1024 - 4096 MLP step).  The tail
+// form alone (degree 8, four instructions fewer, that step 397.5 us against
+// 405.4) is no substitute near zero: the rounding of t enlarged threefold makes it
+// 2.1e-7 off there.  Errors on the device, tail form alone / this / erff:
+//   CDF, largest, |x| <= 6                  2.0e-7 / 6.1e-8 / 7.5e-8
+//   gelu, 2-norm, |x| <= 0.5                9.0e-8 / 3.8e-8 / 4.0e-8
+//   gelu, 2-norm, x from N(0, 1)            3.9e-8 / 3.4e-8 / 3.9e-8
+//   derivative, 2-norm, x from N(0, 1)      6.4e-8 / 3.8e-8 / 4.0e-8
+// The negative tail keeps a relative accuracy where 1 + erf cancels: 7e-7 for x in
+// -3 .. -1.25, then growing with the rounding of x^2 to 3e-6 at -8; 2e-5 at -13.
+// e: exp(-x^2 / 2).
 __device__ __forceinline__ float normal_cdf(float x, float &e) {
-  const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(fabsf(x), 0.262336612f, 1.0f));
-  float q = 0.0319899283f;
-  q = __builtin_fmaf(q, t, -0.155200198f);
-  q = __builtin_fmaf(q, t, 0.248538524f);
-  q = __builtin_fmaf(q, t, -0.149138957f);
-  q = __builtin_fmaf(q, t, 0.160115287f);
-  q = __builtin_fmaf(q, t, 0.0511091352f);
-  q = __builtin_fmaf(q, t, 0.103993565f);
-  q = __builtin_fmaf(q, t, 0.103897266f);
-  q = __builtin_fmaf(q, t, 0.104695439f);
-  e = __builtin_amdgcn_exp2f(x * x * -0.72134752f);
+  const float u = x * x;
+  float q = -6.64486106e-06f;
+  q = __builtin_fmaf(q, u, 0.000110327463f);
+  q = __builtin_fmaf(q, u, -0.00118270959f);
+  q = __builtin_fmaf(q, u, 0.00997150037f);
+  q = __builtin_fmaf(q, u, -0.0664899871f);
+  q = __builtin_fmaf(q, u, 0.398942262f);
+  const float near = __builtin_fmaf(x, q, 0.5f);
+  const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(fabsf(x), 0.318198055f, 1.0f));
+  q = -0.0769115612f;
+  q = __builtin_fmaf(q, t, 0.168941066f);
+  q = __builtin_fmaf(q, t, 0.0227707624f);
+  q = __builtin_fmaf(q, t, 0.134163529f);
+  q = __builtin_fmaf(q, t, 0.123758964f);
+  q = __builtin_fmaf(q, t, 0.127148032f);
+  e = __builtin_amdgcn_exp2f(u * -0.72134752f);
   const float tail = t * q * e;
-  return x < 0.f ? tail : 1.0f - tail;
+  const float far = x < 0.f ? tail : 1.0f - tail;
+  return fabsf(x) < 1.25f ? near : far;
 }
 __device__ __forceinline__ float gelu_fast(float x) {
   float e;

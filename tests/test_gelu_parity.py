@@ -3,8 +3,9 @@ wrong: both signs, zeros, the tails where the CDF leaves fp32's range, values
 whose square overflows, infinities and NaN.  Through pf_gelu_bwd (dH = 1) and
 the forward epilogue of a one-block identity layer, against scipy's erfc in
 float64.  The outputs are bf16 (8 significant bits): half a unit in the last
-place is at most 2^-8 of the value.  On top, the fp32 form's own error: 1e-6
-of the value (the exponential of -x^2 / 2 at |x| = 13), and 1e-6 absolute where
+place is at most 2^-8 of the value.  On top, the fp32 form's own error: 3e-5
+of the value (the fit past its range of 10 and the rounding of x^2 in the
+exponent, at |x| = 13: 2e-5), and 1e-6 absolute where
 CDF and density cancel (the derivative's zero near x = -0.75), falling off
 with the density; an exponential below 2^-126 flushes to zero, which the
 derivative multiplies by |x| (up to 14 before the next bf16 of it is zero too)."""
@@ -35,7 +36,7 @@ def _close(got, ref, x):
     fin = np.isfinite(x) & np.isfinite(ref)
     err = np.abs(got[fin] - ref[fin])
     density = np.exp(-0.5 * np.minimum(x[fin] ** 2, 1400.0))
-    bound = (2.0 ** -8 + 1e-6) * np.abs(ref[fin]) + 1e-6 * density + 15 * 2.0 ** -126
+    bound = (2.0 ** -8 + 3e-5) * np.abs(ref[fin]) + 1e-6 * density + 15 * 2.0 ** -126
     i = int(np.argmax(err - bound))
     assert (err <= bound).all(), (x[fin][i], got[fin][i], ref[fin][i])
 
