@@ -158,9 +158,11 @@ __global__ __launch_bounds__(64 * NW) void small_kernel(SmallArgs a) {
         bb = sp ? spb : lrb;
         ldb = sp ? blk : n.ldr;
       }
-      // Rows past M fall outside A's range; a dead sub-block is pointed out of
-      // every range.  B's rows all exist.
-      const rsrc_t rA = make_rsrc(ab, (n.M - m0) * lda * ES);
+      // Rows past M fall outside A's range, which covers this tile's rows only:
+      // OUT, where a dead sub-block is pointed, then lies outside it however
+      // large the operand (the host keeps 512 rows below 2^31 bytes).  B's rows
+      // all exist.
+      const rsrc_t rA = make_rsrc(ab, min<int64_t>(32, n.M - m0) * lda * ES);
       const rsrc_t rB = make_rsrc(bb, 0x7ffffff0);
       const uint32_t av = a_row * (uint32_t)(lda * ES) + (uint32_t)(acol * ES);
       const uint32_t bv = b_row * (uint32_t)(ldb * ES);

@@ -529,3 +529,33 @@ def test_small_products(n_out, n_in, b, ms, T, r, dtype, gamma, epi):
     if r:
         check_close("T_lr", to_host(Tl), inp["X"] @ V.T, dtype)
         check_close("S", to_host(S), inp["dY"] @ U, dtype)
+
+
+def test_small_product_operand_past_2_gib():
+    """Forward of one 32-column block over an X of more than 2^31 bytes: the
+    K list of one 32-wide block leaves half a step and whole waves dead, and what
+    their copies are pointed at must lie outside X, whose last rows (where
+    2^31 - 16 bytes from the first tile's start falls) are NaN."""
+    torch = torch_cuda()
+    from paper_2112_00029_amd import pixelfly as pf
+    b, nb_in, T, j = 32, 2049, 16384, 7
+    n_in = nb_in * b
+    assert T * n_in * 2 > 2 ** 31 and (T - 16) * n_in * 2 < 2 ** 31 - 16
+    mask = np.zeros((1, nb_in), np.uint8)
+    mask[0, j] = 1
+    L = pf.pf_layout_create_from_mask(1, nb_in, b, mask)
+    pf.pf_layout_upload(L)
+    assert pf.pf_linear_plan_get(L, "bf16", T, 0)["fwd_direct_lds"] == 2
+    print(f"[small 2 GiB] T={T} n_in={n_in}", flush=True)
+    X, Xr = synth.draw((T, b), 1.0, 0, 1, "bf16")
+    W, Wr = synth.draw((1, b, b), 0.2, 0, 2, "bf16")
+    x = torch.zeros((T, n_in), dtype=torch.bfloat16, device="cuda")
+    x[:, j * b:(j + 1) * b] = to_dev(Xr)
+    x[T - 16:] = float("nan")
+    y = empty((T, b), "bf16")
+    pf.pf_linear_fwd(L, "bf16", T, 0, x, to_dev(Wr), None, None, y, None)
+    torch.cuda.synchronize()
+    got = to_host(y)
+    assert np.isfinite(got[:T - 16]).all(), np.argwhere(~np.isfinite(got[:T - 16]))[:4]
+    check_close("Y", got[:T - 16], X[:T - 16] @ W[0].T, "bf16")
+    assert np.isnan(got[T - 16:]).all()
