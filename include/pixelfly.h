@@ -289,7 +289,14 @@ void pf_layout_destroy(pf_layout *layout);
 
 /* Workspace bytes needed by pf_linear_fwd, pf_linear_bwd_data and
  * pf_linear_bwd_weight (the largest of the three) for T tokens and rank r;
- * 0 when none is needed or on invalid arguments. */
+ * 0 when none is needed or on invalid arguments.
+ * A bf16 rank-r product (T_lr, S) of few output tiles runs without one too:
+ * given less room than its K split takes (or a NULL or misaligned workspace)
+ * it takes the kernel that needs none, which sums K in another order.  Its
+ * time, and T_lr and S (and what is computed from them) within a bf16
+ * rounding, thus depend on the workspace given; with the same arguments the
+ * bits are always the same.  pf_linear_plan_get reports the plan for a
+ * workspace of this size. */
 size_t pf_workspace_bytes(const pf_layout *layout, int64_t T, int32_t r,
                           pf_dtype dtype);
 

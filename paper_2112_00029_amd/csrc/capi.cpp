@@ -405,14 +405,16 @@ SkinnyPlan rank_plan(const pf_layout *L, int dtype, int64_t T, int32_t r, bool s
 }
 
 // Plan of a rank-r product for the workspace at hand: a product of few
-// tiles whose split does not fit into ws_bytes (less `extra`, the room its
-// call needs besides) runs on the rank-r kernel, which needs none.
+// tiles whose split has no room there (ws_bytes less `extra`, the room its
+// call needs besides; none in a NULL or misaligned workspace) runs on the
+// rank-r kernel, which needs none.
 SkinnyPlan rank_plan_ws(const pf_layout *L, int dtype, int64_t T, int32_t r, bool s_side,
-                        size_t ws_bytes, size_t extra) {
+                        const void *ws, size_t ws_bytes, size_t extra) {
   SkinnyPlan p = rank_plan(L, dtype, T, r, s_side);
   const int64_t K = s_side ? L->n_out : L->n_in;
   p.skinny = use_skinny(dtype, T, r, K, s_side);
-  if (p.ws > 0 && ws_bytes < (extra ? (p.ws + 255) / 256 * 256 + extra : p.ws) &&
+  const size_t room = ws && aligned16(ws) ? ws_bytes : 0;
+  if (p.ws > 0 && room < (extra ? (p.ws + 255) / 256 * 256 + extra : p.ws) &&
       skinny_small(dtype, T, r, K, s_side)) {
     p.skinny = true;
     p.nsplit = 1;
@@ -1149,7 +1151,7 @@ pf_status linear_fwd(const pf_layout *L, pf_dtype dtype, int64_t T, int32_t r, c
   if (epi != PF_EPI_NONE && epi != PF_EPI_GELU) return fail(PF_ERR_INVALID_ARG, "bad epilogue");
   if (epi == PF_EPI_GELU && (st = need_ptr(Y_pre, "Y_pre")) != PF_OK) return st;
   if (epi == PF_EPI_NONE && Y_pre) return fail(PF_ERR_INVALID_ARG, "Y_pre given without GELU epilogue");
-  const SkinnyPlan sp = rank_plan_ws(L, (int)dtype, T, r, false, ws_bytes, 0);
+  const SkinnyPlan sp = rank_plan_ws(L, (int)dtype, T, r, false, workspace, ws_bytes, 0);
   if ((st = need_ws(sp.ws, workspace, ws_bytes)) != PF_OK) return st;
   if ((st = check_state(L)) != PF_OK) return st;
   hipStream_t s = (hipStream_t)stream;
@@ -1454,7 +1456,7 @@ pf_status pf_linear_bwd_data(const pf_layout *L, pf_dtype dtype, int64_t T, int3
   pf_status st = check_bwd_data_args(L, dtype, T, r, dY, Wblk, U, V, S, dX, epi, aux);
   if (st != PF_OK) return st;
   const size_t pws = pair_ws_bytes(L, (int)dtype, T, r);
-  const SkinnyPlan sp = rank_plan_ws(L, (int)dtype, T, r, true, ws_bytes, pws);
+  const SkinnyPlan sp = rank_plan_ws(L, (int)dtype, T, r, true, workspace, ws_bytes, pws);
   if ((st = need_ws(pws ? align256(sp.ws) + pws : sp.ws, workspace, ws_bytes)) != PF_OK) return st;
   if ((st = check_state(L)) != PF_OK) return st;
   hipStream_t s = (hipStream_t)stream;
@@ -1485,7 +1487,7 @@ pf_status pf_linear_bwd_data_mixed(const pf_layout *L, pf_dtype dtype, int64_t T
   if (st != PF_OK) return st;
   if ((st = check_bwd_data_args(L, dtype, T, r, dY, Wblk, U, V, S, dX, epi, aux)) != PF_OK) return st;
   const size_t pws = pair_ws_bytes(L, (int)dtype, T, r);
-  const SkinnyPlan sp = rank_plan_ws(L, (int)dtype, T, r, true, ws_bytes, pws);
+  const SkinnyPlan sp = rank_plan_ws(L, (int)dtype, T, r, true, workspace, ws_bytes, pws);
   if ((st = need_ws(pws ? align256(sp.ws) + pws : sp.ws, workspace, ws_bytes)) != PF_OK) return st;
   if ((st = check_state(L)) != PF_OK) return st;
   hipStream_t s = (hipStream_t)stream;

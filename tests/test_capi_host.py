@@ -168,6 +168,30 @@ def test_compute_call_errors_before_any_launch():
     pf.pf_gelu_bwd(pf.PF_BF16, 0, None, None, None, stream=0)
 
 
+@pytest.mark.parametrize("ws,n", [(None, 0), (None, 1 << 30), (A16 + 8, 1 << 30), (A16, 256)])
+def test_rank_products_of_few_tiles_need_no_workspace(ws, n):
+    """T_lr and S that split their K range in the workspace, but can run without
+    one: a workspace that cannot hold the split (too small, NULL or misaligned) is
+    ignored and never refused (STATE: the arguments passed, the layout was not
+    uploaded)."""
+    T, r = 2500, 256
+    up, down = pf.pf_layout_create(16384, 32, 32, 1), pf.pf_layout_create(32, 16384, 32, 1)
+    assert pf.pf_linear_plan_get(up, "bf16", T, r)["lowrank_s_split"] > 1
+    assert pf.pf_linear_plan_get(down, "bf16", T, r)["lowrank_t_split"] > 1
+    calls = [
+        lambda: pf.pf_linear_fwd(down, "bf16", T, r, A16, A16, A16, A16, A16, A16, pf.PF_EPI_NONE, None,
+                                 ws, n, stream=0),
+        lambda: pf.pf_linear_bwd_data(up, "bf16", T, r, A16, A16, A16, A16, A16, A16, workspace=ws,
+                                      ws_bytes=n, stream=0),
+        lambda: pf.pf_linear_bwd_data_mixed(up, "bf16", T, r, 0.5, A16, A16, A16, A16, A16, A16,
+                                            workspace=ws, ws_bytes=n, stream=0),
+    ]
+    for f in calls:
+        with pytest.raises(pf.PixelflyError) as e:
+            f()
+        assert e.value.status == pf.PF_ERR_STATE, e.value
+
+
 def test_workspace_sizes():
     L = pf.pf_layout_create(3072, 768, 32, 16)
     ws = pf.pf_workspace_bytes(L, 4096, 96, pf.PF_BF16)
