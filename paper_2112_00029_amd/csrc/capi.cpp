@@ -261,16 +261,21 @@ pf_status dense_nt(pf_kernel_class kc, int dtype, int blk, int G, bool b_kn, int
 // The bf16 rank-r kernel (one launch, no split over workgroups) or the tile
 // kernel (128 x 128 or 256 x 256 tiles, a K split with fp32 partials and a
 // reduction pass).  The rank-r kernel runs a product while 128 x 128 tiles
-// would cover fewer than PF_SKINNY_MAX_TILES of them (a quarter of the CUs)
-// and its busiest compute unit reads at most kSkinnyBytes, about 15 us of
+// would cover fewer than PF_SKINNY_MAX_TILES of them (a quarter of the CUs),
+// where its own 64 x 64 tiles are at most one round of workgroups, and its
+// busiest compute unit reads at most kSkinnyBytes, about 15 us of
 // operand bytes (skinny_tile): with few token rows every workgroup reads its
 // part of the second operand whole, and for deep products the split wins
 // despite its two passes (rank-r kernel / split + reduction, us: 2509 x 4096
 // to r = 256, 1.0 MB, 14.8 / 14.6 + 5; 1500 x 8192 to r = 128, 1.6 MB, 17.6 /
 // 12.3 + 4.5; 128 x 16384 to r = 256, 2.1 MB, 30.9 / 10.1 + 4.6; 2509 x
 // 16384, 4.2 MB, 49 / 35 + 5).
-// S = dY U keeps the rank-r kernel one tile further for K up to 2048 (8192 x
-// 1024 to r = 128: 8.1 us against 9.9 + 5.4).
+// The line of tiles, whole calls with r = 128 (rank-r kernel / tiles, us): T_lr
+// of 8064 tokens (63 tiles, one round) 12.9 / 15.6 at K = 512, 14.8 / 24.1 at 1024,
+// 33.7 / 42.8 at 4096; S 13.4 / 17.0, 16.3 / 25.8, 42.8 / 46.2.  Past a round (8193
+// tokens, 65 tiles) T_lr 17.0 / 16.2, 20.3 / 24.5, 52.5 / 48.9, S 18.9 / 16.7, 23.2 /
+// 25.3, 66.8 / 52.6.  A last full round (64 tiles) and ranks below 128, whose 128-wide
+// tiles are part empty, would still gain (8192 tokens as 8064).
 #ifndef PF_SKINNY_MAX_TILES
 #define PF_SKINNY_MAX_TILES 64
 #endif
@@ -286,13 +291,12 @@ bool skinny_fits(int64_t K, int r) {
   const int64_t lim = 0x7ffffff0LL;
   return 64 * K * 2 < lim && (int64_t)r * K * 2 < lim;
 }
-bool skinny_small(int dtype, int64_t T, int r, int64_t K, bool s_side) {
-  if (dtype != 0 || r <= 0 || !skinny_fits(K, r)) return false;
-  const int64_t tiles = ((T + 127) / 128) * ((r + 127) / 128);
-  return tiles < PF_SKINNY_MAX_TILES + (s_side && K <= 2048 ? 1 : 0);
+bool skinny_small(int dtype, int64_t T, int r, int64_t K) {
+  return dtype == 0 && r > 0 && skinny_fits(K, r) &&
+         ((T + 127) / 128) * ((r + 127) / 128) < PF_SKINNY_MAX_TILES;
 }
 bool use_skinny(int dtype, int64_t T, int r, int64_t K, bool s_side) {
-  return skinny_small(dtype, T, r, K, s_side) &&
+  return skinny_small(dtype, T, r, K) &&
          (K > kSplitMaxK || pf::skinny_tile(s_side, T, r).cost * 2 * K <= kSkinnyBytes);
 }
 
@@ -415,7 +419,7 @@ SkinnyPlan rank_plan_ws(const pf_layout *L, int dtype, int64_t T, int32_t r, boo
   p.skinny = use_skinny(dtype, T, r, K, s_side);
   const size_t room = ws && aligned16(ws) ? ws_bytes : 0;
   if (p.ws > 0 && room < (extra ? (p.ws + 255) / 256 * 256 + extra : p.ws) &&
-      skinny_small(dtype, T, r, K, s_side)) {
+      skinny_small(dtype, T, r, K)) {
     p.skinny = true;
     p.nsplit = 1;
     p.ws = 0;

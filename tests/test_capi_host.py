@@ -168,6 +168,18 @@ def test_compute_call_errors_before_any_launch():
     pf.pf_gelu_bwd(pf.PF_BF16, 0, None, None, None, stream=0)
 
 
+@pytest.mark.parametrize("T", [4096, 8064, 8065, 8192, 8193, 9000])
+def test_rank_products_of_one_depth_take_one_kernel(T):
+    """T_lr of K -> N and S of N -> K are products of the same size, and take the
+    same kernel with the same split on every side of the limits."""
+    for K, r in [(1024, 128), (2048, 128), (4096, 128), (1024, 256), (768, 96), (1024, 64)]:
+        b = 32 if r == 96 else 64
+        p = pf.pf_linear_plan_get(pf.pf_layout_create(512, K, b, 2), "bf16", T, r)
+        q = pf.pf_linear_plan_get(pf.pf_layout_create(K, 512, b, 2), "bf16", T, r)
+        assert (p["lowrank_t_kernel"], p["lowrank_t_split"]) == \
+            (q["lowrank_s_kernel"], q["lowrank_s_split"]), (T, K, r, p, q)
+
+
 @pytest.mark.parametrize("ws,n", [(None, 0), (None, 1 << 30), (A16 + 8, 1 << 30), (A16, 256)])
 def test_rank_products_of_few_tiles_need_no_workspace(ws, n):
     """T_lr and S that split their K range in the workspace, but can run without
