@@ -269,7 +269,8 @@ pf_status dense_nt(pf_kernel_class kc, int dtype, int blk, int G, bool b_kn, int
 // despite its two passes (rank-r kernel / split + reduction, us: 2509 x 4096
 // to r = 256, 1.0 MB, 14.8 / 14.6 + 5; 1500 x 8192 to r = 128, 1.6 MB, 17.6 /
 // 12.3 + 4.5; 128 x 16384 to r = 256, 2.1 MB, 30.9 / 10.1 + 4.6; 2509 x
-// 16384, 4.2 MB, 49 / 35 + 5).
+// 16384, 4.2 MB, 49 / 35 + 5; 64 tokens to r = 128 from 65536 78 / 9.2 + 14.8,
+// from 2^20 3338 / 140 + 57).
 // The line of tiles, whole calls with r = 128 (rank-r kernel / tiles, us): T_lr
 // of 8064 tokens (63 tiles, one round) 12.9 / 15.6 at K = 512, 14.8 / 24.1 at 1024,
 // 33.7 / 42.8 at 4096; S 13.4 / 17.0, 16.3 / 25.8, 42.8 / 46.2.  Past a round (8193
@@ -280,9 +281,6 @@ pf_status dense_nt(pf_kernel_class kc, int dtype, int blk, int G, bool b_kn, int
 #define PF_SKINNY_MAX_TILES 64
 #endif
 constexpr int64_t kSkinnyBytes = 5 << 18;
-// Products deeper than this (the split was measured to 16384) keep the rank-r
-// kernel.
-constexpr int64_t kSplitMaxK = 65536;
 // It addresses its operands through 32-bit buffer ranges and points what
 // lies past the end at the offset 0x7ffffff0, which must lie outside every
 // range: A's tile (64 K-long rows) and the whole r x K (or K x r) second
@@ -297,7 +295,7 @@ bool skinny_small(int dtype, int64_t T, int r, int64_t K) {
 }
 bool use_skinny(int dtype, int64_t T, int r, int64_t K, bool s_side) {
   return skinny_small(dtype, T, r, K) &&
-         (K > kSplitMaxK || pf::skinny_tile(s_side, T, r).cost * 2 * K <= kSkinnyBytes);
+         pf::skinny_tile(s_side, T, r).cost * 2 * K <= kSkinnyBytes;
 }
 
 // bf16 rank-r product C[M x r] = A[M x K] . op(B) on the rank-r kernel

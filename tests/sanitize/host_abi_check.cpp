@@ -173,8 +173,9 @@ int main() {
     }
   }
   // A token split whose rounding to whole steps would pass 2^31 bytes per
-  // split, and a rank-r product whose second operand exceeds the rank-r
-  // kernel's 32-bit range (tile kernel instead).
+  // split, and rank-r products 2^20 deep: both split their K range, and only the
+  // one whose second operand lies in the rank-r kernel's 32-bit range may run
+  // there when it has no workspace (STATE: the arguments passed).
   {
     pf_layout *L = nullptr;
     {
@@ -192,7 +193,14 @@ int main() {
     EXPECT(pf_linear_plan_get(W, PF_BF16, 64, 1024, &p) == PF_OK);
     EXPECT(p.lowrank_t_kernel == 2);
     EXPECT(pf_linear_plan_get(W, PF_BF16, 64, 128, &p) == PF_OK);
-    EXPECT(p.lowrank_t_kernel == 1);
+    EXPECT(p.lowrank_t_kernel == 2 && p.lowrank_t_split > 1);
+    void *const at = (void *)0x10000;
+    auto fwd = [&](int32_t r) {
+      return pf_linear_fwd(W, PF_BF16, 64, r, at, at, at, at, at, at, PF_EPI_NONE, nullptr, nullptr, 0,
+                           nullptr);
+    };
+    EXPECT(fwd(1024) == PF_ERR_WORKSPACE);
+    EXPECT(fwd(128) == PF_ERR_STATE);
     pf_layout *X = nullptr;
     {
       const pf_status st_ = pf_layout_create(1024, 1 << 22, 128, 8, &X);

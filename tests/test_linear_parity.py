@@ -450,13 +450,14 @@ def test_rank_kernel_tiles(T, n_in, n_out, r, t_tile, s_tile):
     check_close("S", got["S"], ref["S"], "bf16")
 
 
-def test_deep_rank_product_without_workspace():
-    """S = dY U, 16384 deep at 2500 tokens and r = 256 (few tiles, split over K
-    by plan): given no workspace it runs on the rank-r kernel, and agrees with
-    the split."""
+@pytest.mark.parametrize("T,n_out,r", [(2500, 16384, 256), (65, 65664, 128)])
+def test_deep_rank_product_without_workspace(T, n_out, r):
+    """S = dY U, 16384 deep at 2500 tokens and r = 256 and 65664 deep at 65 tokens
+    (few tiles, split over K by plan): given no workspace it runs on the rank-r
+    kernel, and agrees with the split."""
     torch = torch_cuda()
     from paper_2112_00029_amd import pixelfly as pf
-    T, n_in, n_out, r, b = 2500, 32, 16384, 256, 32
+    n_in, b = 32, 32
     inp = _inputs(n_out, n_in, b, 1, T, r, "bf16")
     L = pf.pf_layout_create(n_out, n_in, b, 1)
     pf.pf_layout_upload(L)
