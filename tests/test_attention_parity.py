@@ -96,10 +96,12 @@ def test_attention_global_every_row():
     _run(1, 2, 512, 8, heads=[(0, 0), (0, 1)], g=8)
 
 
-def test_attention_global_rows_shorter_than_groups():
-    """Two key blocks per row: two of the four groups of the forward / dQ
-    kernels own no block and must contribute nothing."""
-    _run(1, 2, 128, 2, heads=[(0, 0), (0, 1)], g=1)
+@pytest.mark.parametrize("S,ms", [(128, 2), (384, 4), (448, 8)])
+def test_attention_global_rows_shorter_than_groups(S, ms):
+    """Stripes of 6 and 7 key blocks on the grouped kernels: two (one) of the eight
+    groups of the forward / dQ own no block and must contribute nothing.  Two key
+    blocks (under six): the stripe's rows run with the others."""
+    _run(1, 2, S, ms, heads=[(0, 0), (0, 1)], g=1)
 
 
 def test_attention_single_block_sequence():
@@ -137,28 +139,47 @@ def test_attention_repeat_calls_bitwise():
             assert torch.equal(r[name], runs[0][name]), name
 
 
+MOVING_MASKS = {
+    # 16 blocks in 6 rows (1 .. 5 each): one group per row, single stage.
+    "one group": ["100000", "110000", "101010", "111100", "111110", "000010"],
+    # 35 blocks in 8 rows (at least four per row on average): two groups per row,
+    # double-buffered; rows of 1 (the second group empty), 2, odd and even counts.
+    "two groups": ["00100000", "10000010", "01010100", "11101000", "11111110", "01111100",
+                   "11111110", "10111110"],
+}
+
+
 @pytest.mark.parametrize("order", ["growing", "shrinking"])
-def test_attention_moving_reference_and_empty_columns(order):
+@pytest.mark.parametrize("kind", ["one group", "two groups", "stripe of 7", "stripe of 16"])
+def test_attention_moving_reference_and_empty_columns(kind, order):
     """Scores that grow (shrink) from key block to key block by far more than
-    the forward's rescale threshold, in both halves of a block, on a mask with
-    rows of 1 .. 5 blocks (odd and even counts of the double-buffered loops)
-    and one key block that no query attends (zero dK, dV)."""
+    the forward's rescale threshold, in both halves of a block: on masks with rows
+    of few and many blocks and one key block that no query attends (zero dK, dV), and
+    under a global stripe, whose row's groups (eight in the forward and dQ; 7 blocks
+    leave one of them empty) merge references that lie far apart."""
     torch = torch_cuda()
     from paper_2112_00029_amd import pixelfly as pf
-    B, H, nb, d, b = 1, 2, 6, 64, 64
+    B, H, d, b = 1, 2, 64, 64
+    print(f"[attn-moving] {kind} {order}", flush=True)
+    if kind in MOVING_MASKS:
+        mask = np.array([[int(c) for c in row] for row in MOVING_MASKS[kind]], np.uint8)
+        nb = len(mask)
+        L = pf.pf_layout_create_from_mask(nb, nb, b, mask)
+        assert (mask.sum() >= 4 * nb) == (kind == "two groups") and not mask[:, -1].any()
+    else:
+        nb = int(kind.split()[-1])
+        L = pf.pf_layout_create_attention(nb * b, b, 4, 1)
+        mask = om.attention_layout(nb * b, b, 4, 1)[0].astype(np.uint8)
     S = nb * b
-    print(f"[attn-moving] {order}", flush=True)
-    mask = np.array([[1, 0, 0, 0, 0, 0], [1, 1, 0, 0, 0, 0], [1, 0, 1, 0, 1, 0],
-                     [1, 1, 1, 1, 0, 0], [1, 1, 1, 1, 1, 0], [0, 0, 0, 0, 1, 0]], np.uint8)
     raw = {n: synth.draw((B, H, S, d), 1.0, 9, sid, "bf16") for n, sid in
            (("Q", 11), ("K", 12), ("V", 13), ("dO", 14))}
     # Powers of two per 32 keys (exact in bf16), 1/4 .. 4: scores of 4 x N(0, 1),
     # a maximum near 8 (11 in log2 units, past the threshold of 8).
     g = 2.0 ** (np.arange(2 * nb) // 2 - 2 + (np.arange(2 * nb) % 2))
-    g = np.minimum(g if order == "growing" else g[::-1], 4.0).repeat(32)[:, None]
+    g = np.minimum(g, 4.0)
+    g = (g if order == "growing" else g[::-1]).repeat(32)[:, None]
     K = raw["K"][0] * g
     Kr = synth.bf16_bits_from_f32(K.astype(np.float32))
-    L = pf.pf_layout_create_from_mask(nb, nb, b, mask)
     pf.pf_layout_upload(L)
     q, k, v, do = to_dev(raw["Q"][1]), to_dev(Kr), to_dev(raw["V"][1]), to_dev(raw["dO"][1])
     O, dQ, dK, dV = (empty((B, H, S, d), "bf16") for _ in range(4))
@@ -168,7 +189,8 @@ def test_attention_moving_reference_and_empty_columns(order):
     ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
     pf.pf_attn_bwd(L, B, H, S, d, 0.125, q, k, v, O, lse, do, dQ, dK, dV, ws, wsb)
     torch.cuda.synchronize()
-    assert not to_host(dK)[:, :, 5 * b:].any() and not to_host(dV)[:, :, 5 * b:].any()
+    empty_cols = np.repeat(~mask.any(0), b)
+    assert not to_host(dK)[:, :, empty_cols].any() and not to_host(dV)[:, :, empty_cols].any()
     Mel = om.element_mask(mask.astype(bool), b)
     for h in range(H):
         Qh, Kh, Vh, dOh = raw["Q"][0][0, h], K[0, h], raw["V"][0][0, h], raw["dO"][0][0, h]
