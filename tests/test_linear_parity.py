@@ -149,10 +149,16 @@ def test_linear_parity(n_out, n_in, b, ms, T, r, dtype):
         check_close(k, got[k], ref[k], dtype)
 
 
-def test_fp32_integer_inputs_bit_exact():
+@pytest.mark.parametrize("T,r,family", [(256, 32, 2), (2100, 256, 0)])
+def test_fp32_integer_inputs_bit_exact(T, r, family):
     """Integer inputs in [-2, 2], fp32 I/O: every partial sum is an integer
-    below 2^24, so the GPU result equals the oracle exactly."""
-    n_out, n_in, b, ms, T, r = 1024, 1024, 32, 32, 256, 32
+    below 2^24, so the GPU result equals the oracle exactly.  On the small-product
+    kernel and on the large tiles, whose rank-r products split K."""
+    from paper_2112_00029_amd import pixelfly as pf
+    n_out, n_in, b, ms = 1024, 1024, 32, 32
+    plan = pf.pf_linear_plan_get(pf.pf_layout_create(n_out, n_in, b, ms), "fp32", T, r)
+    assert (plan["fwd_direct_lds"], plan["bwd_direct_lds"]) == (family, family), plan
+    assert (plan["lowrank_t_split"] > 1) == (family == 0), plan
     inp = _inputs(n_out, n_in, b, ms, T, r, "fp32", ints=(-2, 2))
     got, _ = _run_gpu(n_out, n_in, b, ms, T, r, "fp32", inp)
     ref = _oracle(inp, r, b)
@@ -495,6 +501,41 @@ def test_small_products(n_out, n_in, b, ms, T, r, dtype, gamma, epi):
     """Forward and backward-data on the small-product kernel (32 x 32 output
     tiles, K list split over the waves): ragged tokens, dead steps, the
     switch to the low-rank blocks, every epilogue."""
+    plan = _check_epilogues(n_out, n_in, b, ms, T, r, dtype, gamma, epi)
+    assert (plan["fwd_direct_lds"], plan["bwd_direct_lds"]) == (2, 2), plan
+    assert r == 0 or plan["lowrank_t_kernel"] == plan["lowrank_s_kernel"] == (3 if dtype == "fp32" else 1)
+
+
+@pytest.mark.parametrize("n_out,n_in,b,ms,T,r,gamma,epi,rank", [
+    # tiles of one and of several block columns; plain, GELU, mixed
+    (1024, 800, 32, 8, 700, 0, None, 0, None),
+    (1536, 768, 32, 16, 700, 64, None, 1, "small"),
+    (1024, 800, 32, 8, 700, 96, 0.6, 1, "small"),
+    (2048, 1024, 64, 8, 1100, 64, None, 1, "small"),
+    (1152, 1024, 64, 4, 1100, 128, 0.35, 0, "small"),
+    (1024, 1152, 128, 4, 1100, 128, None, 1, "small"),
+    (2048, 1024, 128, 8, 1100, 128, 0.7, 0, "small"),
+    # rank-r products on the tiles without a split (few K steps)
+    (96, 160, 32, 2, 5500, 96, None, 0, "tile"),
+    # rank-r products on the split tiles and the fp32 row reduction: a rank
+    # below one 128-column tile (both token tiles), and above
+    (512, 544, 32, 4, 5500, 96, None, 0, "split"),
+    (512, 576, 64, 4, 8200, 64, None, 0, "split"),
+    (1024, 2048, 64, 8, 2100, 256, None, 1, "split"),
+])
+def test_fp32_large_products(n_out, n_in, b, ms, T, r, gamma, epi, rank):
+    """fp32 forward and backward-data past the small-product kernel's range
+    (register-staged tiles), with every epilogue, at ragged token counts."""
+    plan = _check_epilogues(n_out, n_in, b, ms, T, r, "fp32", gamma, epi)
+    assert (plan["fwd_direct_lds"], plan["bwd_direct_lds"]) == (0, 0), plan
+    if rank:
+        assert plan["lowrank_t_kernel"] == plan["lowrank_s_kernel"] == (3 if rank == "small" else 2), plan
+        assert (plan["lowrank_t_split"] > 1) == (plan["lowrank_s_split"] > 1) == (rank == "split"), plan
+
+
+def _check_epilogues(n_out, n_in, b, ms, T, r, dtype, gamma, epi):
+    """Forward and backward-data, plain or mixed (gamma), with (epi) the GELU and
+    GELU' epilogues, against the oracle's products; returns the plan."""
     torch = torch_cuda()
     from paper_2112_00029_amd import pixelfly as pf
     std = (1.0, 1.0 / np.sqrt(6 * 32), 1.0 / 32, 1.0) if dtype == "fp32" else (0.02,) * 4
@@ -502,9 +543,7 @@ def test_small_products(n_out, n_in, b, ms, T, r, dtype, gamma, epi):
     L = pf.pf_layout_create(n_out, n_in, b, ms)
     pf.pf_layout_upload(L)
     plan = pf.pf_linear_plan_get(L, dtype, T, r)
-    print(f"[small] {n_out}x{n_in} b={b} T={T} r={r} {dtype} gamma={gamma} epi={epi}", flush=True)
-    assert (plan["fwd_direct_lds"], plan["bwd_direct_lds"]) == (2, 2), plan
-    assert r == 0 or plan["lowrank_t_kernel"] == plan["lowrank_s_kernel"] == (3 if dtype == "fp32" else 1)
+    print(f"[epilogues] {n_out}x{n_in} b={b} T={T} r={r} {dtype} gamma={gamma} epi={epi}", flush=True)
     d = {k: to_dev(v) for k, v in inp["raw"].items()}
     H, Hr = synth.draw((T, n_in), 1.0, 0, 40, dtype)
     aux = to_dev(Hr) if epi else None
@@ -515,8 +554,11 @@ def test_small_products(n_out, n_in, b, ms, T, r, dtype, gamma, epi):
     lead = (L, dtype, T, r) if gamma is None else (L, dtype, T, r, gamma)
     fwd = pf.pf_linear_fwd if gamma is None else pf.pf_linear_fwd_mixed
     bwd = pf.pf_linear_bwd_data if gamma is None else pf.pf_linear_bwd_data_mixed
-    fwd(*lead, d["X"], d["W"], d["U"] if r else None, d["V"] if r else None, Y, Tl, e, pre)
-    bwd(*lead, d["dY"], d["W"], d["U"] if r else None, d["V"] if r else None, S, dX, e, aux)
+    # Without a split no product needs a workspace.
+    wsb = pf.pf_workspace_bytes(L, T, r, dtype) if plan["lowrank_t_split"] > 1 or plan["lowrank_s_split"] > 1 else 0
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda") if wsb else None
+    fwd(*lead, d["X"], d["W"], d["U"] if r else None, d["V"] if r else None, Y, Tl, e, pre, ws, wsb)
+    bwd(*lead, d["dY"], d["W"], d["U"] if r else None, d["V"] if r else None, S, dX, e, aux, ws, wsb)
     torch.cuda.synchronize()
     a, be = (1.0, 1.0) if gamma is None else (gamma, 1.0 - gamma)
     Wd, U, V = inp["Wd"], inp["U"], inp["V"]
@@ -530,6 +572,7 @@ def test_small_products(n_out, n_in, b, ms, T, r, dtype, gamma, epi):
     if r:
         check_close("T_lr", to_host(Tl), inp["X"] @ V.T, dtype)
         check_close("S", to_host(S), inp["dY"] @ U, dtype)
+    return plan
 
 
 def test_small_product_operand_past_2_gib():
