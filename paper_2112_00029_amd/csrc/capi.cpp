@@ -427,8 +427,8 @@ SkinnyPlan rank_plan_ws(const pf_layout *L, int dtype, int64_t T, int32_t r, boo
 
 // Split-token plan of the TN kernel.  Few work items (under one round of
 // kTNSlots resident workgroups): the split of at most PF_TN_MAX_SPLIT parts of
-// at least min_tokens tokens that minimises rounds x steps per workgroup.  Many
-// items: aim for about 4096 workgroups (token splits also shorten each
+// at least 512 (fp32: 64) tokens that minimises rounds x steps per workgroup
+// (bf16: and the partials' traffic).  Many items: aim for about 4096 workgroups (token splits also shorten each
 // workgroup's serial chain and its L2 footprint) with power-of-two splits of
 // at least 512 tokens, at most PF_TN_MAX_SPLIT, keeping the fp32 partial
 // traffic in check.  Always enough splits that one split's rows stay below
@@ -455,12 +455,11 @@ struct TNPlan {
   size_t pair_off = 0;
 };
 
-// row_bytes: the largest operand row stride in bytes.
-int64_t tn_min_tokens(int dtype) { return dtype == 0 ? 512 : 64; }
-
-// min_tokens: fewest tokens per split (512 for bf16, whose weight gradient
-// is bound by operand traffic; 64 for fp32, bound by its long MFMAs).
-TNPlan tn_plan(int items, int64_t T, int64_t row_bytes, int64_t min_tokens = 512) {
+// row_bytes: the largest operand row stride in bytes.  Fewest tokens per split:
+// 512 for bf16, whose weight gradient is bound by operand traffic; 64 for
+// fp32, bound by its long MFMAs.
+TNPlan tn_plan(int dtype, int items, int64_t T, int64_t row_bytes) {
+  const int64_t min_tokens = dtype == 0 ? 512 : 64;
   TNPlan p{1, ((T + 63) / 64) * 64, 0};
   const int64_t min_split = (T * row_bytes + 0x7fffffffLL - 1) / 0x7fffffffLL;
   int64_t ns = 1;
@@ -477,7 +476,7 @@ TNPlan tn_plan(int items, int64_t T, int64_t row_bytes, int64_t min_tokens = 512
     for (int64_t c = 1; c <= cap; ++c) {
       const int64_t chunk = ((T + c - 1) / c + 63) / 64 * 64, nsr = (T + chunk - 1) / chunk;
       int64_t cost = ((items * nsr + kTNSlots - 1) / kTNSlots) * (chunk / 64) * 52;
-      if (min_tokens == 512 && nsr > 1) cost += nsr * items;
+      if (dtype == 0 && nsr > 1) cost += nsr * items;
       if (best < 0 || cost < best) {
         best = cost;
         ns = nsr;
@@ -1012,7 +1011,7 @@ size_t pf_workspace_bytes(const pf_layout *L, int64_t T, int32_t r, pf_dtype dty
   const int items = pf::tn_items_total(a, L->b);
   // The 128 x 128 plan (mixed calls, and the rest when the wide kernel does
   // not apply) and, where it applies, the 256 x 256 one.
-  const size_t tn = tn_plan(items, T, std::max(L->n_out, L->n_in) * es, tn_min_tokens(dtype)).ws;
+  const size_t tn = tn_plan(dtype, items, T, std::max(L->n_out, L->n_in) * es).ws;
   size_t tnw = 0;
   if (tn_wide(L, (int)dtype, T, r, false) || tn_pairs(L, (int)dtype, T, r, false)) {
     TNPlan wp;
@@ -1404,8 +1403,8 @@ pf::TNArgs tn_args(const pf_layout *L, pf_dtype dtype, int64_t T, int32_t r, con
   } else {
     a.items = L->d_tn_items; a.n_items = (int)L->tn_items.size();
     set_tn_order(a, L, L->tn_items, 128 / L->b);
-    *plan = tn_plan(pf::tn_items_total(a, L->b), T,
-                    std::max(L->n_out, L->n_in) * (dtype == PF_BF16 ? 2 : 4), tn_min_tokens(dtype));
+    *plan = tn_plan(dtype, pf::tn_items_total(a, L->b), T,
+                    std::max(L->n_out, L->n_in) * (dtype == PF_BF16 ? 2 : 4));
   }
   a.nsplit = plan->nsplit;
   a.chunk = plan->chunk;
@@ -1745,7 +1744,7 @@ size_t pf_dense_workspace_bytes(pf_dtype dtype, pf_gemm_op op, int64_t M, int64_
   if (dtype != PF_BF16 && dtype != PF_FP32) return 0;
   if (op != PF_OP_TN || M < 64 || N < 64 || K < 1 || M % 64 || N % 64) return 0;
   int items = (int)(((M / 64 + 1) / 2) * ((N / 64 + 1) / 2));
-  return tn_plan(items, K, std::max(M, N) * (dtype == PF_BF16 ? 2 : 4), tn_min_tokens(dtype)).ws;
+  return tn_plan(dtype, items, K, std::max(M, N) * (dtype == PF_BF16 ? 2 : 4)).ws;
 }
 
 // Blocks of 64 columns per dense comparator tile: 256-wide bf16 tiles when
@@ -1783,8 +1782,8 @@ pf_status pf_dense_gemm(pf_dtype dtype, pf_gemm_op op, int64_t M, int64_t N, int
       a.dr[0] = pf::TNDense{A, M, B, N, C, N, (int)(M / 64), (int)(N / 64)};
       a.n_dense = 1;
       a.T = K;
-      TNPlan p = tn_plan(pf::tn_items_total(a, 64), K, std::max(M, N) * (dtype == PF_BF16 ? 2 : 4),
-                         tn_min_tokens(dtype));
+      TNPlan p = tn_plan(dt, pf::tn_items_total(a, 64), K,
+                         std::max(M, N) * (dtype == PF_BF16 ? 2 : 4));
       if ((st = need_ws(p.ws, workspace, ws_bytes)) != PF_OK) return st;
       a.nsplit = p.nsplit;
       a.chunk = p.chunk;

@@ -1001,9 +1001,9 @@ __global__ __launch_bounds__(256) void gelu_bwd_kernel(int64_t n, const T *dH, c
 // ---------------------------------------------------------------------------
 // Launchers.  The build compiles this file once per part (PF_GK_PART): 0
 // holds the small kernels and the dispatch, 1-4 the NT kernel for (bf16 |
-// fp32) x (B as [n][k] | [k][n]), 5-6 the TN kernel for bf16 | fp32, so that
-// the template instantiations compile in parallel.  Without PF_GK_PART the
-// file holds everything.
+// fp32) x (B as [n][k] | [k][n]), 5-6 the pass over split TN partials for bf16 |
+// fp32 and, in 6, the fp32 TN kernel, so that the template instantiations
+// compile in parallel.  Without PF_GK_PART the file holds everything.
 // ---------------------------------------------------------------------------
 
 template <typename T, int BLK, int G, bool BKN, int BM, bool DENSE>
@@ -1101,8 +1101,6 @@ hipError_t launch_tn_f32(int blk, const TNArgs &a, hipStream_t s) {
   }
   return hipErrorInvalidValue;
 }
-#else
-hipError_t launch_tn_f32(int blk, const TNArgs &a, hipStream_t s);
 #endif
 template <typename T>
 hipError_t launch_tn_reduce_t(int blk, const TNArgs &a, hipStream_t s) {

@@ -228,15 +228,13 @@ hipError_t launch_tnw_reduce(int blk, int shared, const TNArgs &a, hipStream_t s
 // each): T is uint16_t (bf16 storage) or float.
 template <typename T, bool BKN>
 hipError_t launch_nt_tb(int blk, int G, int bm, bool dense, const NTArgs &a, hipStream_t s);
-template <typename T>
-hipError_t launch_tn_t(int blk, const TNArgs &a, hipStream_t s);
+hipError_t launch_tn_f32(int blk, const TNArgs &a, hipStream_t s);
 template <typename T>
 hipError_t launch_tn_reduce_t(int blk, const TNArgs &a, hipStream_t s);
 extern template hipError_t launch_nt_tb<uint16_t, false>(int, int, int, bool, const NTArgs &, hipStream_t);
 extern template hipError_t launch_nt_tb<uint16_t, true>(int, int, int, bool, const NTArgs &, hipStream_t);
 extern template hipError_t launch_nt_tb<float, false>(int, int, int, bool, const NTArgs &, hipStream_t);
 extern template hipError_t launch_nt_tb<float, true>(int, int, int, bool, const NTArgs &, hipStream_t);
-extern template hipError_t launch_tn_t<float>(int, const TNArgs &, hipStream_t);
 extern template hipError_t launch_tn_reduce_t<uint16_t>(int, const TNArgs &, hipStream_t);
 extern template hipError_t launch_tn_reduce_t<float>(int, const TNArgs &, hipStream_t);
 // Work items of a TN launch on tile x tile tiles (128 or 256).
