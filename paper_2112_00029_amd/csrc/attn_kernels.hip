@@ -181,7 +181,7 @@ __device__ __forceinline__ void attn_order(int L, int BH, int nb, int nlong, int
 // workgroup) and the groups' softmax states (reference, sum, unnormalised O)
 // are merged through LDS in group order at the end.
 template <int NG, int ST>
-__global__ __launch_bounds__(128 * NG, NG == 1 && ST == 1 ? 4 : 1) void attn_fwd_kernel(AttnArgs a) {
+__global__ __launch_bounds__(128 * NG, ST == 1 ? 4 : 1) void attn_fwd_kernel(AttnArgs a) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 1);
   const int grp = NG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 7) : 0;
@@ -275,22 +275,21 @@ __global__ __launch_bounds__(128 * NG, NG == 1 && ST == 1 ? 4 : 1) void attn_fwd
       }
   };
   if constexpr (ST == 1) {
-    for (int it = 0; it < iters; ++it) {
-      const int p = p0 + it * NG + grp;
-      const bool valid = NG == 1 || p < p1;
+    static_assert(NG == 1 || ST == 2, "groups are double-buffered");
+    for (int p = p0; p < p1; ++p) {
       wait_vm<0>();  // this wave's K copies have landed,
       barrier();     // every wave's have, and the last block's V is read
-      cp.issue(V + (int64_t)ccur * BQ * D, v0s, p < p1);
+      cp.issue(V + (int64_t)ccur * BQ * D, v0s, true);
       scores(k0s);
       wait_vm<4>();  // (no wait: the four V copies may be in flight)
       barrier();     // every wave has read K
-      cp.issue(K + (int64_t)cn * BQ * D, k0s, p + NG < p1);
+      cp.issue(K + (int64_t)cn * BQ * D, k0s, p + 1 < p1);
       ccur = cn;
-      cn = ld_meta(a.col_idx + min(p + 2 * NG, p1 - 1));
-      if (valid) softmax();
+      cn = ld_meta(a.col_idx + min(p + 2, p1 - 1));
+      softmax();
       wait_vm<4>();  // V has landed; the next K copies stay in flight
       barrier();
-      if (valid) product(v0s);
+      product(v0s);
     }
   } else {
     uint8_t *const k1s = stage_buf<2, NG * TILE>() + grp * TILE;
@@ -372,7 +371,7 @@ __global__ __launch_bounds__(128 * NG, NG == 1 && ST == 1 ? 4 : 1) void attn_fwd
 // NG groups split the row's kept blocks as in the forward; their dQ partial
 // sums are added through LDS in group order.
 template <int NG, int ST>
-__global__ __launch_bounds__(128 * NG, NG == 1 && ST == 1 ? 4 : 1) void attn_bwd_dq_kernel(AttnArgs a) {
+__global__ __launch_bounds__(128 * NG, ST == 1 ? 4 : 1) void attn_bwd_dq_kernel(AttnArgs a) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 1);
   const int grp = NG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 7) : 0;
@@ -450,25 +449,22 @@ __global__ __launch_bounds__(128 * NG, NG == 1 && ST == 1 ? 4 : 1) void attn_bwd
     }
   };
   if constexpr (ST == 1) {
-    for (int it = 0; it < iters; ++it) {
-      const int p = p0 + it * NG + grp;
-      const bool valid = NG == 1 || p < p1;
+    static_assert(NG == 1 || ST == 2, "groups are double-buffered");
+    for (int p = p0; p < p1; ++p) {
       wait_vm<0>();  // this wave's copies of the block have landed,
       barrier();     // every wave's have
       const int cc = cn;
-      cn = ld_meta(a.col_idx + min(p + 2 * NG, p1 - 1));
-      if (valid) {
-        scores(k0s, v0s, 0);
-        grads(k0s, 0);
-        scores(k0s, v0s, 1);
-      }
+      cn = ld_meta(a.col_idx + min(p + 2, p1 - 1));
+      scores(k0s, v0s, 0);
+      grads(k0s, 0);
+      scores(k0s, v0s, 1);
       wait_vm<0>();
       barrier();  // every wave has read V
-      cp.issue(V + (int64_t)cc * BQ * D, v0s, p + NG < p1);
-      if (valid) grads(k0s, 1);
+      cp.issue(V + (int64_t)cc * BQ * D, v0s, p + 1 < p1);
+      grads(k0s, 1);
       wait_vm<4>();
       barrier();  // every wave has read K
-      cp.issue(K + (int64_t)cc * BQ * D, k0s, p + NG < p1);
+      cp.issue(K + (int64_t)cc * BQ * D, k0s, p + 1 < p1);
     }
   } else {
     uint8_t *const k1s = stage_buf<2, NG * TILE>() + grp * TILE;
@@ -687,6 +683,13 @@ __global__ __launch_bounds__(128 * NG) void attn_bwd_dkv_kernel(AttnArgs a) {
 // two groups, two stages (us): 12 heads x 1024, 5 blocks per row (192
 // workgroups), dQ 9.7 / 7.6; 24 heads (384) forward 8.3 / 7.7, dQ 11.7 /
 // 10.5; 48 heads (768) forward 9.6 / 11.6, dQ 13.5 / 15.1.
+//
+// The grouped kernels take four groups in two stages.  Eight groups in one
+// stage, as many waves and bytes of LDS per block in flight, pay for a longer
+// merge and a wait per operand.  12 heads x 384 / 1024 / 4096, one stripe, forward
+// + dQ of both launches, us, with 16-row waves in four groups / eight groups / four
+// groups: 30.7 / 35.7 / 30.2, 39.1 / 43.4 / 36.6, 85.4 / 78.0 / 69.5; 96 heads 33.3 /
+// 38.9 / 33.0, 59.0 / 58.7 / 51.0, 181 / 166 / 155.
 namespace {
 constexpr int64_t kAttnFewWG = 512;
 template <typename F1, typename FG>
@@ -715,13 +718,13 @@ hipError_t attn_launch(F1 plain, F1 few, int nfew, FG grouped, int ng, AttnArgs 
 }  // namespace
 
 hipError_t launch_attn_fwd(const AttnArgs &a, int part, hipStream_t s) {
-  return attn_launch(attn_fwd_kernel<1, 1>, attn_fwd_kernel<2, 2>, 2, attn_fwd_kernel<8, 1>, 8, a,
+  return attn_launch(attn_fwd_kernel<1, 1>, attn_fwd_kernel<2, 2>, 2, attn_fwd_kernel<4, 2>, 4, a,
                      part, s);
 }
 
 hipError_t launch_attn_bwd_dq(const AttnArgs &a, int part, hipStream_t s) {
   return attn_launch(attn_bwd_dq_kernel<1, 1>, attn_bwd_dq_kernel<2, 2>, 2,
-                     attn_bwd_dq_kernel<8, 1>, 8, a, part, s);
+                     attn_bwd_dq_kernel<4, 2>, 4, a, part, s);
 }
 
 hipError_t launch_attn_bwd_dkv(const AttnArgs &a, int part, hipStream_t s) {

@@ -98,9 +98,9 @@ def test_attention_global_every_row():
 
 @pytest.mark.parametrize("S,ms", [(128, 2), (384, 4), (448, 8)])
 def test_attention_global_rows_shorter_than_groups(S, ms):
-    """Stripes of 6 and 7 key blocks on the grouped kernels: two (one) of the eight
-    groups of the forward / dQ own no block and must contribute nothing.  Two key
-    blocks (under six): the stripe's rows run with the others."""
+    """Stripes of 6 and 7 key blocks on the grouped kernels, whose four groups own two
+    blocks or one.  Two key blocks (under six): the stripe's rows run with the
+    others."""
     _run(1, 2, S, ms, heads=[(0, 0), (0, 1)], g=1)
 
 
@@ -155,8 +155,8 @@ def test_attention_moving_reference_and_empty_columns(kind, order):
     """Scores that grow (shrink) from key block to key block by far more than
     the forward's rescale threshold, in both halves of a block: on masks with rows
     of few and many blocks and one key block that no query attends (zero dK, dV), and
-    under a global stripe, whose row's groups (eight in the forward and dQ; 7 blocks
-    leave one of them empty) merge references that lie far apart."""
+    under a global stripe, whose row's four groups merge references that lie far
+    apart."""
     torch = torch_cuda()
     from paper_2112_00029_amd import pixelfly as pf
     B, H, d, b = 1, 2, 64, 64
