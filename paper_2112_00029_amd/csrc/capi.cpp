@@ -1551,10 +1551,14 @@ pf_status pf_gelu_bwd(pf_dtype dtype, int64_t n, const void *dH, const void *H_p
 }
 
 // Leading block rows (columns) of the global stripes that run on the grouped
-// kernels, in a launch of their own: none when whole rows are short enough
-// for the plain kernels (72 heads x 128, one stripe: dQ 9.0 us in two launches, 6.0
-// in one; 48 heads x 512: 11.5 against 14.1).
-static int attn_long_rows(const pf_layout *L) { return L->nb_out < 6 ? 0 : L->global_blocks; }
+// kernels, in a launch of their own: none for sequences of fewer than 12
+// blocks, whose whole rows are short enough for the plain kernels, in one launch with
+// the other rows.  One stripe, forward + backward in two launches each / in one, us:
+// 12 heads x 512 (8 blocks) 44.7 / 25.3, 48 heads 52.4 / 36.0, 128 heads 68.1 / 56.5; at
+// 10 blocks 128 heads 82.5 / 68.8; at 12 12 heads 50.6 / 33.0, 96 heads 83.7 / 75.1, but
+// with stride 1 (short other rows) 65.8 / 68.0; at 16 12 heads 55.3 / 40.7, 96 heads 105.6 /
+// 117.8, stride 1 78.4 / 108.9.
+static int attn_long_rows(const pf_layout *L) { return L->nb_out < 12 ? 0 : L->global_blocks; }
 
 static pf_status attn_check(const pf_layout *L, int32_t B, int32_t H, int32_t Sq, int32_t d) {
   pf_status st = check_layout_arg(L);

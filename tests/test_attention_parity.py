@@ -90,17 +90,18 @@ def test_attention_global_wide_stripes_small_stride():
     _run(1, 2, 1024, 4, heads=[(0, 0), (0, 1)], g=3)
 
 
-def test_attention_global_every_row():
-    """Stripes as wide as the sequence: every block row is long (only the
-    grouped kernels run) and the mask is dense."""
-    _run(1, 2, 512, 8, heads=[(0, 0), (0, 1)], g=8)
+@pytest.mark.parametrize("S,g", [(512, 8), (832, 13)])
+def test_attention_global_every_row(S, g):
+    """Stripes as wide as the sequence: the mask is dense, and every block row is
+    long (from 12 blocks on, only the grouped kernels run)."""
+    _run(1, 2, S, 8, heads=[(0, 0), (0, 1)], g=g)
 
 
-@pytest.mark.parametrize("S,ms", [(128, 2), (384, 4), (448, 8)])
-def test_attention_global_rows_shorter_than_groups(S, ms):
-    """Stripes of 6 and 7 key blocks on the grouped kernels, whose four groups own two
-    blocks or one.  Two key blocks (under six): the stripe's rows run with the
-    others."""
+@pytest.mark.parametrize("S,ms", [(128, 2), (384, 4), (448, 8), (704, 2), (768, 4), (832, 8)])
+def test_attention_global_rows_around_the_grouped_kernels(S, ms):
+    """Stripes of sequences under twelve blocks, whose rows run with the others, and
+    of 12 and 13 blocks on the grouped kernels (four groups with equal and unequal
+    shares)."""
     _run(1, 2, S, ms, heads=[(0, 0), (0, 1)], g=1)
 
 
@@ -150,13 +151,13 @@ MOVING_MASKS = {
 
 
 @pytest.mark.parametrize("order", ["growing", "shrinking"])
-@pytest.mark.parametrize("kind", ["one group", "two groups", "stripe of 7", "stripe of 16"])
+@pytest.mark.parametrize("kind", ["one group", "two groups", "stripe of 7", "stripe of 13"])
 def test_attention_moving_reference_and_empty_columns(kind, order):
     """Scores that grow (shrink) from key block to key block by far more than
     the forward's rescale threshold, in both halves of a block: on masks with rows
     of few and many blocks and one key block that no query attends (zero dK, dV), and
-    under a global stripe, whose row's four groups merge references that lie far
-    apart."""
+    under a global stripe, whose row runs with the others (7 blocks) or on four
+    groups (13) that merge references which lie far apart."""
     torch = torch_cuda()
     from paper_2112_00029_amd import pixelfly as pf
     B, H, d, b = 1, 2, 64, 64
