@@ -678,11 +678,14 @@ __global__ __launch_bounds__(128 * NG) void attn_bwd_dkv_kernel(AttnArgs a) {
 //
 // `few` (two groups per block row, two stages per operand) is the plain kernel
 // of launches of at most two workgroups per CU: nothing else runs on the CU
-// then, and a row's serial chain of blocks is the time.  Rows of fewer than
-// four blocks on average do not repay the merge.  One group, one stage /
-// two groups, two stages (us): 12 heads x 1024, 5 blocks per row (192
-// workgroups), dQ 9.7 / 7.6; 24 heads (384) forward 8.3 / 7.7, dQ 11.7 /
-// 10.5; 48 heads (768) forward 9.6 / 11.6, dQ 13.5 / 15.1.
+// then, and a row's serial chain of blocks is the time.  It takes rows of two
+// blocks and more on average while no CU has a second workgroup, of three and a
+// half and more up to two.  One group, one stage / two groups, two stages, forward and
+// dQ (us): 144 workgroups, 2 blocks per row 4.3 + 5.9 / 4.3 + 5.5, 3 blocks 4.7 +
+// 6.6 / 4.7 + 6.0; 384 workgroups, 2 blocks 5.0 + 7.2 / 5.4 + 7.6, 3 blocks 6.4 + 8.8 / 6.4 +
+// 8.7, 3.7 blocks 6.7 + 9.8 / 6.6 + 8.9; 768 workgroups, 5 blocks 9.6 + 13.5 / 11.6 + 15.1.
+// The average is of the launch's own rows: a stripe's long rows, in a launch of
+// their own, say nothing about the others.
 //
 // The grouped kernels take four groups in two stages.  Eight groups in one
 // stage, as many waves and bytes of LDS per block in flight, pay for a longer
@@ -695,7 +698,12 @@ constexpr int64_t kAttnFewWG = 512;
 template <typename F1, typename FG>
 hipError_t attn_launch(F1 plain, F1 few, int nfew, FG grouped, int ng, AttnArgs a, int part,
                        hipStream_t s) {
-  int64_t grid;
+  // Block rows of the launch and their kept blocks (a long row keeps all).
+  int64_t grid, rows = a.nbq, nnzb = a.nnzb;
+  if (part == 2) {
+    rows -= a.nlong;
+    nnzb -= (int64_t)a.nlong * a.nbq;
+  }
   if (part == 1) {
     grid = (int64_t)a.BH * a.nlong;
     a.first = 0;
@@ -709,7 +717,7 @@ hipError_t attn_launch(F1 plain, F1 few, int nfew, FG grouped, int ng, AttnArgs 
   if (grid <= 0 || grid > 0x7fffffff) return hipErrorInvalidValue;
   if (part == 1)
     launch_kernel(grouped, dim3((unsigned)grid), dim3(128 * ng), s, a);
-  else if (grid <= kAttnFewWG && a.nnzb >= 4 * (int64_t)a.nbq)
+  else if (grid <= kAttnFewWG && 2 * nnzb >= (grid <= kAttnFewWG / 2 ? 4 : 7) * rows)
     launch_kernel(few, dim3((unsigned)grid), dim3(128 * nfew), s, a);
   else
     launch_kernel(plain, dim3((unsigned)grid), dim3(128), s, a);

@@ -141,17 +141,20 @@ def test_attention_repeat_calls_bitwise():
 
 
 MOVING_MASKS = {
-    # 16 blocks in 6 rows (1 .. 5 each): one group per row, single stage.
-    "one group": ["100000", "110000", "101010", "111100", "111110", "000010"],
-    # 35 blocks in 8 rows (at least four per row on average): two groups per row,
+    # 15 blocks in 8 rows (under two per row on average): one group per row, single
+    # stage.
+    "one group": ["10000000", "11000000", "10101000", "01000000", "11110000", "00001000",
+                  "01000010", "00000100"],
+    # 16 blocks in 6 rows (1 .. 5 each) and 35 in 8: two groups per row,
     # double-buffered; rows of 1 (the second group empty), 2, odd and even counts.
-    "two groups": ["00100000", "10000010", "01010100", "11101000", "11111110", "01111100",
-                   "11111110", "10111110"],
+    "two groups": ["100000", "110000", "101010", "111100", "111110", "000010"],
+    "two groups, longer rows": ["00100000", "10000010", "01010100", "11101000", "11111110",
+                                "01111100", "11111110", "10111110"],
 }
 
 
 @pytest.mark.parametrize("order", ["growing", "shrinking"])
-@pytest.mark.parametrize("kind", ["one group", "two groups", "stripe of 7", "stripe of 13"])
+@pytest.mark.parametrize("kind", [*MOVING_MASKS, "stripe of 7", "stripe of 13"])
 def test_attention_moving_reference_and_empty_columns(kind, order):
     """Scores that grow (shrink) from key block to key block by far more than
     the forward's rescale threshold, in both halves of a block: on masks with rows
@@ -166,7 +169,7 @@ def test_attention_moving_reference_and_empty_columns(kind, order):
         mask = np.array([[int(c) for c in row] for row in MOVING_MASKS[kind]], np.uint8)
         nb = len(mask)
         L = pf.pf_layout_create_from_mask(nb, nb, b, mask)
-        assert (mask.sum() >= 4 * nb) == (kind == "two groups") and not mask[:, -1].any()
+        assert (mask.sum() >= 2 * nb) == (kind != "one group") and not mask[:, -1].any()
     else:
         nb = int(kind.split()[-1])
         L = pf.pf_layout_create_attention(nb * b, b, 4, 1)
