@@ -177,21 +177,29 @@ __global__ __launch_bounds__(64 * NW) void small_kernel(SmallArgs a) {
     });
   };
 
-  f32x16 acc;
+  // fp32: two accumulators, the even and the odd steps of the wave, so that no
+  // chain of sums is longer than the tile kernel's K split leaves it (128 terms below
+  // 1024 deep): T_lr of 512 x 896 to r = 64 is 2.1e-7 off by that split, 2.7e-7 with one
+  // accumulator, 2.0e-7 so (0.2 us a launch).
+  constexpr int NACC = ES == 4 ? 2 : 1;
+  f32x16 acc[NACC];
 #pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+  for (int e = 0; e < 16; ++e) acc[0][e] = acc[NACC - 1][e] = 0.f;
   // Mixing weight: this wave's kept-block sums are scaled once, before its
   // first low-rank K slice or after its last step.
   bool scale = n.mix != 0;
   auto rescale = [&]() __attribute__((always_inline)) {
+    sfor<NACC>([&](auto q) __attribute__((always_inline)) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] *= n.mix_ratio;
+      for (int e = 0; e < 16; ++e) acc[q][e] *= n.mix_ratio;
+    });
     scale = false;
   };
   const int kswitch = nsteps << lb;
   // D rows = output columns, D columns = tokens: lane l ends with token l % 32
   // and columns (e / 4) * 8 + (l / 32) * 4 + e % 4.
-  auto compute = [&](int i, const uint8_t *da, const uint8_t *db) __attribute__((always_inline)) {
+  auto compute = [&](int i, auto j, const uint8_t *da, const uint8_t *db) __attribute__((always_inline)) {
+    f32x16 &sum = acc[decltype(j)::value % NACC];
     const int s = w + i * NW;
     sfor<NH>([&](auto h) __attribute__((always_inline)) {
       if (scale && (s * NH + h) * KW >= kswitch) rescale();
@@ -201,24 +209,24 @@ __global__ __launch_bounds__(64 * NW) void small_kernel(SmallArgs a) {
           bf16x8 wf;
           if constexpr (BKN) wf = frag_kn<RBB>(db + h * SUB, 0, kq, lane);
           else wf = frag_rows<RBB>(db + h * SUB, 0, kq, lane);
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, xf, acc, 0, 0, 0);
+          sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, xf, sum, 0, 0, 0);
         });
       } else {
-        // Lane half h takes the K chunks 2 j + h (4 values): the MFMAs of j
-        // visit k = 8 j + 4 h + 0..3.
+        // Lane half h takes the K chunks 2 c + h (4 values): the MFMAs of c
+        // visit k = 8 c + 4 h + 0..3.
         const int r = lane & 31, hf = lane >> 5, sw = swz_row<8>(r);
-        sfor<4>([&](auto j) __attribute__((always_inline)) {
-          const f32x4 x = *(const f32x4 *)(da + r * 128 + (((2 * j + hf) ^ sw) << 4));
+        sfor<4>([&](auto c) __attribute__((always_inline)) {
+          const f32x4 x = *(const f32x4 *)(da + r * 128 + (((2 * c + hf) ^ sw) << 4));
           f32x4 b;
           if constexpr (BKN) {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-              b[q] = *(const float *)(db + (8 * j + 4 * hf + q) * 128 + r * 4);
+              b[q] = *(const float *)(db + (8 * c + 4 * hf + q) * 128 + r * 4);
           } else {
-            b = *(const f32x4 *)(db + r * 128 + (((2 * j + hf) ^ sw) << 4));
+            b = *(const f32x4 *)(db + r * 128 + (((2 * c + hf) ^ sw) << 4));
           }
 #pragma unroll
-          for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(b[q], x[q], acc, 0, 0, 0);
+          for (int q = 0; q < 4; ++q) sum = __builtin_amdgcn_mfma_f32_32x32x2f32(b[q], x[q], sum, 0, 0, 0);
         });
       }
     });
@@ -231,7 +239,7 @@ __global__ __launch_bounds__(64 * NW) void small_kernel(SmallArgs a) {
   for (int i = 0; i < steps; i += 2) {
     sfor<2>([&](auto j) __attribute__((always_inline)) {
       wait_vm<DPS>();
-      compute(i + j, stage_a(j), stage_b(j));
+      compute(i + j, j, stage_a(j), stage_b(j));
       wait_vm<DPS>();  // (LDS reads returned)
       issue(i + 2 + j, stage_a(j), stage_b(j));
     });
@@ -244,7 +252,8 @@ __global__ __launch_bounds__(64 * NW) void small_kernel(SmallArgs a) {
   __syncthreads();
   float *const red = (float *)stage_buf<0, NW * 4096>();
 #pragma unroll
-  for (int e = 0; e < 16; ++e) red[w * 1024 + e * 64 + lane] = acc[e];
+  for (int e = 0; e < 16; ++e)
+    red[w * 1024 + e * 64 + lane] = NACC == 2 ? acc[0][e] + acc[NACC - 1][e] : acc[0][e];
   __syncthreads();
   if (!elive) return;
   float v[4] = {0.f, 0.f, 0.f, 0.f};

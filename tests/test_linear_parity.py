@@ -575,6 +575,29 @@ def _check_epilogues(n_out, n_in, b, ms, T, r, dtype, gamma, epi):
     return plan
 
 
+@pytest.mark.parametrize("K", [544, 768, 896, 992, 1024])
+def test_fp32_rank_product_error(K):
+    """fp32 T_lr and S up to 1024 deep sum no more than 128 terms in one chain: a
+    chain of n random terms ends sqrt(n / 2) average roundings (0.41 x 2^-24 of the
+    sum) off, 2.0e-7 at 128, and the few sums of chains add little to it: 2.3e-7 at
+    most (at 224 terms 2.6e-7)."""
+    torch = torch_cuda()
+    from paper_2112_00029_amd import pixelfly as pf
+    T, r, b = 512, 64, 32
+    g = torch.Generator(device="cuda").manual_seed(K)
+    draw = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    x, v, u, t = draw(T, K), draw(r, K), draw(K, r), empty((T, r), "fp32")
+    out, w = empty((T, b), "fp32"), torch.zeros((K // b, b, b), device="cuda")
+    print(f"[fp32 rank error] K={K}", flush=True)
+    down, up = pf.pf_layout_create(b, K, b, 1), pf.pf_layout_create(K, b, b, 1)
+    for L in (down, up):
+        pf.pf_layout_upload(L)
+    pf.pf_linear_fwd(down, "fp32", T, r, x, w, torch.zeros((b, r), device="cuda"), v, out, t)
+    assert rel_fro(to_host(t), to_host(x) @ to_host(v).T) <= 2.3e-7
+    pf.pf_linear_bwd_data(up, "fp32", T, r, x, w, u, torch.zeros((r, b), device="cuda"), t, out)
+    assert rel_fro(to_host(t), to_host(x) @ to_host(u)) <= 2.3e-7
+
+
 def test_small_product_operand_past_2_gib():
     """Forward of one 32-column block over an X of more than 2^31 bytes: the
     K list of one 32-wide block leaves half a step and whole waves dead, and what
