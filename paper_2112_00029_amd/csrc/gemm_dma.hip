@@ -450,29 +450,27 @@ __global__ __launch_bounds__(64 * NW, OCC) void ntd_kernel(NTArgs a_arg) {
     });
     return;
   }
-  // GELU backward: the pre-activations of a pass are loaded one pass ahead.
-  // Loaded where they are used, each of the sixteen row groups of a 256 x
-  // 256 tile waited a memory round trip of its own (8192 x 4096: 80.5 ->
-  // 71 us).  Rows past M and dead columns read zero (range check), so the
-  // loads need no branch.
+  // GELU backward: the pre-activations of a pass are loaded before its sums are
+  // staged.  Rows past M and dead columns read zero (range check), so the loads
+  // need no branch.  (A pass further ahead, in two sets of registers, is no faster: 8192
+  // x 4096 66.4 us so, 66.7 that way.)
   constexpr int NPASS = TM * (32 / SP), NIT = SP / RPI;
-  u32x4 ax[2][EPI == 2 ? NIT : 1];
+  u32x4 ax[EPI == 2 ? NIT : 1];
   const rsrc_t rx = make_rsrc(EPI == 2 ? (const bf16_t *)a.aux + m0 * a.ldc : nullptr,
                               EPI == 2 ? (a.M - m0) * a.ldc * 2 : 0);
   auto load_aux = [&](auto pass) __attribute__((always_inline)) {
-    if constexpr (EPI == 2 && decltype(pass)::value < NPASS) {
+    if constexpr (EPI == 2) {
       constexpr int tm = pass / (32 / SP), half = pass % (32 / SP);
       sfor<NIT>([&](auto it) __attribute__((always_inline)) {
         const uint32_t row = (uint32_t)(wm * WTM + tm * 32 + half * SP + it * RPI + rl);
         const uint32_t off = col_ok ? (row * (uint32_t)a.ldc + (uint32_t)col) * 2u : 0x7ffffff0u;
-        ax[pass & 1][it] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)off, 0, 0);
+        ax[it] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)off, 0, 0);
       });
     }
   };
-  load_aux(std::integral_constant<int, 0>{});
   sfor<NPASS>([&](auto pass) __attribute__((always_inline)) {
     constexpr int tm = pass / (32 / SP), half = pass % (32 / SP);
-    load_aux(std::integral_constant<int, pass + 1>{});
+    load_aux(pass);
     if ((lane & 31) / SP == half) {
       const int r = (lane & 31) % SP;
       sfor<TN>([&](auto tn) __attribute__((always_inline)) {
@@ -508,7 +506,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void ntd_kernel(NTArgs a_arg) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = gelu_fast(v[e]);
       } else if constexpr (EPI == 2) {  // backward GELU: scale by gelu'(pre-activation)
-        const u32x4 x = ax[pass & 1][it];
+        const u32x4 x = ax[it];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           v[2 * e] *= gelu_grad_fast(__uint_as_float(x[e] << 16));
