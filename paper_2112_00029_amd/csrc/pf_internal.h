@@ -244,10 +244,10 @@ hipError_t launch_skinny(bool b_kn, const SkinnyArgs &a, hipStream_t s);
 // of them, a workgroup each at a time) reads the fewest operand bytes,
 // rounds x (m + n) rows of K; on ties the larger tile, and 64 x 32 for
 // B [n][k], 32 x 64 for B [k][n], whose rows of 32 columns are half a cache
-// line (2100 x 4096 to r = 128: 13.1 against 16.5 us).  A compute unit takes
+// line (S of 2100 x 4096 to r = 128: 12.3 against 15.3 us).  A compute unit takes
 // in about 88 bytes per ns however many copies are in flight, so that sum is
-// the time: 2509 x 4096 to r = 256 takes 13.9 us on 64 x 64 tiles, 21.4 on
-// 32 x 64; 4096 x 3072 to r = 96 13.1 us on 32 x 64, 15.1 on 64 x 64.
+// the time: T_lr of 2509 x 4096 to r = 256 takes 14.0 us on 64 x 64 tiles, 22.1 on
+// 32 x 64; S of 4096 x 3072 to r = 96 11.2 us on 32 x 64, 14.6 on 64 x 64.
 struct SkinnyTile {
   int m, n;
   int64_t cost;  // rounds x (m + n): times 2 K, the bytes of the busiest unit

@@ -19,9 +19,10 @@
 // region, chunks XOR-swizzled so that the MFMA operand reads and the
 // transpose reads of a [k][n] B (U) have no bank conflicts.  Reading the
 // operands from global memory in MFMA layout instead (16 rows of 32 bytes
-// per request; before / now): 4096 x 768 to r = 96 8.3 / 6.9 us, 4096 x 3072
-// 15.4 / 12.9, 1024 x 8192 to r = 256 28.2 / 19.7, 512 x 4096 to r = 64
-// 26.6 / 7.0.
+// per request; before / now, the kernel in a loop over one call): T_lr of 4096 x
+// 768 to r = 96 6.6 / 5.7 us, 4096 x 3072 19.7 / 8.7, 1024 x 8192 to r = 256 48.6 / 13.7,
+// 2509 x 4096 to r = 256 52.2 / 13.9; S of 4096 x 3072 to r = 96 12.8 / 10.9, 512 x 4096
+// to r = 64 14.8 / 7.5.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -210,7 +211,7 @@ hipError_t skinny_go(const SkinnyArgs &a, hipStream_t s) {
 
 template <bool BKN>
 hipError_t skinny_pick(const SkinnyArgs &a, hipStream_t s) {
-  // Long K: as many waves as the LDS holds (T x K of 2100 x 4096 to r = 128:
+  // Long K: as many waves as the LDS holds (S of 2100 x 4096 to r = 128:
   // 13.1 us with six waves, 15.6 with four); short K: four, whose few steps
   // each need no third stage.
   const bool deep = a.K >= 48 * SK_BK;
