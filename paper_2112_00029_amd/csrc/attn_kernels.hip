@@ -20,8 +20,8 @@
 // tiles from LDS whatever its row count, so 32 rows per wave halve the LDS
 // bytes per score of the 16-row waves these kernels had before, and the
 // swizzled tiles have no bank conflicts.  Counters at 8 x 12 x 4096 x 64,
-// 7 blocks per row: forward VALU 51 % (exponentials a third of it), MFMA
-// 29 %, LDS 15 % of cycles; dQ 42 / 32 / 16 %, dK/dV 39 / 33 / 25 %: the
+// 7 blocks per row: forward VALU 53 % (exponentials three tenths of it), MFMA
+// 31 %, LDS 15 % of cycles; dQ 43 / 32 / 16 %, dK/dV 39 / 37 / 28 %: the
 // serial S -> softmax -> product chain of few waves per SIMD bounds them, so
 // forward and dQ keep one stage per operand (16 KiB per workgroup, four
 // waves per SIMD; two stages and 2.5 waves: 79 against 66 us, 111 against
